@@ -53,8 +53,9 @@ enum {
 };
 
 /*
- * Tuning and mode options.  A NULL pointer, or 0 in a field, selects the
- * built-in default for that field.
+ * Tuning and mode options of the merge sort.  A NULL pointer, or 0 in a field,
+ * selects the built-in default for that field (see below for the sorts that
+ * take digit passes when no field is set).
  *   keys_per_lane   R, keys each lane sorts in VGPRs: 8, 16 or 32 (Sec. 2.2
  *                   picks 16 registers for NEON; here R is a VGPR budget);
  *                   4 for key sorts (the smallest row of Table 2).
@@ -133,6 +134,15 @@ const char *hvms_status_string(int status);
 int hvms_last_hip_error(void);
 
 /* ------------------------------------------------------------------ sort */
+
+/*
+ * Calls whose options leave everything to the library (NULL, or every field
+ * 0) sort large arrays by stable passes over 8-bit digits instead of merge
+ * passes: keys alone and sorts by key from 2^16 keys, pairs and 64-bit keys
+ * from 2^22 to 3 * 2^24.  The result is the same bit for bit.  Any option set
+ * (a tile shape, a co-rank mode, stats, events, ...) keeps the merge sort, and
+ * so does a workspace that only holds what the merge sort needs.
+ */
 
 /* Bytes of workspace hvms_sort_i32 / hvms_sort_pairs_i32 need for n keys
  * (pairs != 0 for key-value sorts).  Returns a negative status on error. */

@@ -453,10 +453,21 @@ def hvms_cdf_sample_i32(keys, m, seed, out, stream=None):
 
 # -------------------------------------------------- allocating conveniences
 
+# sizes from which the library's own choice (digit passes) beats every merge
+# shape, so no tuned shape is asked for: first and last n of each kind of sort
+_DIGIT_PASSES = {"sort": (1 << 16, 2**32 - 2**16), "sort_by_key": (1 << 16, 2**31 - 1),
+                 "sort_pairs": (1 << 22, 3 << 24)}
+
+
 def _auto(op, n, opts):
-    """Explicit options win; otherwise the autotuner's cached entry, if any."""
+    """Explicit options win; then the sizes the library's own choice is best
+    at; otherwise the autotuner's cached entry, if any."""
     if opts is not None:
         return opts
+    lo, hi = _DIGIT_PASSES.get(op, (1, 0))
+    if lo <= n <= hi:
+        return None
+    op = "sort_pairs" if op == "sort_by_key" else op
     from . import tune
     return tune.tuned_options(op, n)
 
@@ -533,7 +544,7 @@ def sort_pairs_keys(keys, vals, keys_out=None, vals_out=None, opts=None, stream=
 def sort_by_key(keys, vals, keys_out=None, vals_out=None, opts=None, stream=None):
     """Stable sort of int32 keys carrying 64-bit payloads (vals: any 8-byte
     dtype); equal keys keep their input order.  keys_out may be keys."""
-    opts = _auto("sort_pairs", keys.numel(), opts)
+    opts = _auto("sort_by_key", keys.numel(), opts)
     keys_out = torch.empty_like(keys) if keys_out is None else keys_out
     vals_out = torch.empty_like(vals) if vals_out is None else vals_out
     ws = _workspace(lib().hvms_sort_by_key_workspace_bytes(keys.numel(), _opts(opts)),

@@ -132,6 +132,46 @@ SortWs sort_ws_layout(int64_t n, bool pairs, const Cfg &c, bool packed = false)
     return w;
 }
 
+// Whether a call leaves every choice to the library: no option that picks a
+// merge shape, a co-rank mode, statistics or tracing.
+bool library_choice(const hvms_options *o)
+{
+    return !o || !(o->keys_per_lane || o->block_threads || o->wave_levels || o->merge_tile ||
+                   o->corank_mode || o->radius_log2 || o->cdf_params || o->stats || o->events ||
+                   o->n_events || o->merge_variant || o->merge_occupancy || o->column_network ||
+                   o->merge_ways);
+}
+
+// Sizes that take the digit passes (radix.hip) where the choice is the
+// library's.  Keys alone and the sort by key: from 2^16 keys, where their
+// twelve launches meet the merge sort's (2^15 uniform keys 47 against 37 us,
+// 2^16 46 against 50, 2^20 64 against 109, 2^28 3.4 against 5.7 ms).  Two-word
+// elements make up to eight passes: from 2^22 (pairs of any order there 0.21
+// against 0.25-0.31 ms; at 2^21 presorted keys are even) up to 3 * 2^24, past
+// which their runs go to HBM in pieces and random pairs lose (2^25 1.23 against
+// 1.69 ms, 2^26 2.78 against 2.60).
+constexpr int64_t kRadixMin = 1 << 16, kRadixMin2 = 1 << 22, kRadixMax2 = 3 << 24;
+constexpr int64_t kRadixMax = ((int64_t)1 << 32) - (1 << 16);  // 32-bit positions
+bool radix_route(int kind, int64_t n, const hvms_options *o)
+{
+    const bool two = kind == RADIX_PAIRS || kind == RADIX_KEYS64;
+    return n >= (two ? kRadixMin2 : kRadixMin) && n <= (two ? kRadixMax2 : kRadixMax) &&
+           library_choice(o);
+}
+
+// Workspace of a sort by either route.  A pair sort's has room for the digit
+// passes of a sort by key of the same size too (whose workspace is the pair
+// sort's and one index array).
+int64_t sort_need(int kind, int64_t n, const Cfg &c, const hvms_options *o)
+{
+    const int64_t m =
+        sort_ws_layout(n, kind != RADIX_KEYS, c, kind == RADIX_KEYS64).total;
+    const bool digits = radix_route(kind, n, o) ||
+                        (kind == RADIX_PAIRS && radix_route(RADIX_BY_KEY, n, o));
+    const int64_t r = digits ? radix_layout(kind, n).total : 0;
+    return m > r ? m : r;
+}
+
 int check_ws(void *ws, size_t bytes, int64_t need)
 {
     if (need == 0)
@@ -233,6 +273,25 @@ int run_sort(bool pairs, const int32_t *kin, const int32_t *vin, int32_t *kout, 
     return HVMS_OK;
 }
 
+// A sort by the route its options, size and workspace allow: a workspace too
+// small for the digit passes (one sized for the merge passes by an explicit
+// option set) takes the merge passes.
+int sort_any(int kind, const void *kin, const int32_t *vin, void *kout, int32_t *vout, int64_t n,
+             void *ws, size_t ws_bytes, hipStream_t s, const Cfg &c, const hvms_options *opt,
+             KeyMap km = {})
+{
+    if (radix_route(kind, n, opt) && (int64_t)ws_bytes >= radix_layout(kind, n).total) {
+        RadixIO io{};
+        io.kin = kin;
+        io.vin = vin;
+        io.kout = kout;
+        io.vout = vout;
+        return hip_status(launch_radix(kind, io, n, ws, km, s));
+    }
+    return run_sort(kind != RADIX_KEYS, (const int32_t *)kin, vin, (int32_t *)kout, vout, n, ws,
+                    s, c, km);
+}
+
 }  // namespace
 
 extern "C" {
@@ -260,7 +319,7 @@ int64_t hvms_sort_workspace_bytes(int64_t n, int32_t pairs, const hvms_options *
     const int st = resolve(opt, pairs != 0, c);
     if (st)
         return st;
-    return sort_ws_layout(n, pairs != 0, c).total;
+    return sort_need(pairs ? RADIX_PAIRS : RADIX_KEYS, n, c, opt);
 }
 
 int hvms_sort_i32(const int32_t *d_in, int32_t *d_out, int64_t n, void *d_ws, size_t ws_bytes,
@@ -277,7 +336,8 @@ int hvms_sort_i32(const int32_t *d_in, int32_t *d_out, int64_t n, void *d_ws, si
     st = check_ws(d_ws, ws_bytes, sort_ws_layout(n, false, c).total);
     if (st)
         return st;
-    return run_sort(false, d_in, nullptr, d_out, nullptr, n, d_ws, (hipStream_t)stream, c);
+    return sort_any(RADIX_KEYS, d_in, nullptr, d_out, nullptr, n, d_ws, ws_bytes,
+                    (hipStream_t)stream, c, opt);
 }
 
 }  // extern "C"
@@ -342,7 +402,8 @@ int hvms_sort_i32_noalloc(const int32_t *d_in, int32_t *d_out, int64_t n, void *
         if (st)
             return st;
     }
-    return run_sort(false, d_in, nullptr, d_out, nullptr, n, ws, (hipStream_t)stream, c);
+    return sort_any(RADIX_KEYS, d_in, nullptr, d_out, nullptr, n, ws,
+                    HVMS_SORT_NOALLOC_SCRATCH_BYTES, (hipStream_t)stream, c, opt);
 }
 
 int hvms_sort_pairs_i32(const int32_t *d_keys_in, const int32_t *d_vals_in, int32_t *d_keys_out,
@@ -360,8 +421,8 @@ int hvms_sort_pairs_i32(const int32_t *d_keys_in, const int32_t *d_vals_in, int3
     st = check_ws(d_ws, ws_bytes, sort_ws_layout(n, true, c).total);
     if (st)
         return st;
-    return run_sort(true, d_keys_in, d_vals_in, d_keys_out, d_vals_out, n, d_ws,
-                    (hipStream_t)stream, c);
+    return sort_any(RADIX_PAIRS, d_keys_in, d_vals_in, d_keys_out, d_vals_out, n, d_ws, ws_bytes,
+                    (hipStream_t)stream, c, opt);
 }
 
 }  // extern "C"
@@ -392,8 +453,8 @@ int sort_keys_mapped(const void *d_in, void *d_out, int64_t n, void *d_ws, size_
     st = check_ws(d_ws, ws_bytes, sort_ws_layout(n, false, c).total);
     if (st)
         return st;
-    return run_sort(false, (const int32_t *)d_in, nullptr, (int32_t *)d_out, nullptr, n, d_ws,
-                    (hipStream_t)stream, c, key_map_of(kind));
+    return sort_any(RADIX_KEYS, d_in, nullptr, d_out, nullptr, n, d_ws, ws_bytes,
+                    (hipStream_t)stream, c, opt, key_map_of(kind));
 }
 
 int sort_pairs_mapped(const void *d_keys_in, const int32_t *d_vals_in, void *d_keys_out,
@@ -411,8 +472,8 @@ int sort_pairs_mapped(const void *d_keys_in, const int32_t *d_vals_in, void *d_k
     st = check_ws(d_ws, ws_bytes, sort_ws_layout(n, true, c).total);
     if (st)
         return st;
-    return run_sort(true, (const int32_t *)d_keys_in, d_vals_in, (int32_t *)d_keys_out,
-                    d_vals_out, n, d_ws, (hipStream_t)stream, c, key_map_of(kind));
+    return sort_any(RADIX_PAIRS, d_keys_in, d_vals_in, d_keys_out, d_vals_out, n, d_ws, ws_bytes,
+                    (hipStream_t)stream, c, opt, key_map_of(kind));
 }
 
 KeyMap key_map64_of(int kind)  // 0 int64, 1 uint64, 2 float64
@@ -444,8 +505,8 @@ int sort_keys64(const void *d_in, void *d_out, int64_t n, void *d_ws, size_t ws_
     st = check_ws(d_ws, ws_bytes, sort_ws_layout(n, true, c, true).total);
     if (st)
         return st;
-    return run_sort(true, (const int32_t *)d_in, nullptr, (int32_t *)d_out, nullptr, n, d_ws,
-                    (hipStream_t)stream, c, key_map64_of(kind));
+    return sort_any(RADIX_KEYS64, d_in, nullptr, d_out, nullptr, n, d_ws, ws_bytes,
+                    (hipStream_t)stream, c, opt, key_map64_of(kind));
 }
 
 }  // namespace
@@ -460,7 +521,7 @@ int64_t hvms_sort64_workspace_bytes(int64_t n, const hvms_options *opt)
     const int st = resolve(opt, true, c);
     if (st)
         return st;
-    return sort_ws_layout(n, true, c, true).total;
+    return sort_need(RADIX_KEYS64, n, c, opt);
 }
 
 int hvms_sort_i64(const int64_t *d_in, int64_t *d_out, int64_t n, void *d_ws, size_t ws_bytes,
@@ -491,7 +552,7 @@ int64_t hvms_sort_by_key_workspace_bytes(int64_t n, const hvms_options *opt)
         return st;
     if (n == 0)
         return 0;
-    return align256(n * 4) + sort_ws_layout(n, true, c).total;
+    return align256(n * 4) + sort_need(RADIX_PAIRS, n, c, opt);
 }
 
 int hvms_sort_by_key_i32_p64(const int32_t *d_keys_in, const uint64_t *d_vals_in,
@@ -517,6 +578,16 @@ int hvms_sort_by_key_i32_p64(const int32_t *d_keys_in, const uint64_t *d_vals_in
     st = check_ws(d_ws, ws_bytes, idx_bytes + sort_ws_layout(n, true, c).total);
     if (st)
         return st;
+    if (radix_route(RADIX_BY_KEY, n, opt) &&
+        (int64_t)ws_bytes >= radix_layout(RADIX_BY_KEY, n).total) {
+        RadixIO io{};
+        io.kin = d_keys_in;
+        io.kout = d_keys_out;
+        io.pin = d_vals_in;
+        io.pout = d_vals_out;
+        return hip_status(
+            launch_radix(RADIX_BY_KEY, io, n, d_ws, KeyMap{}, (hipStream_t)stream));
+    }
     int32_t *idx = (int32_t *)d_ws;
     KeyMap km;
     km.iota = true;

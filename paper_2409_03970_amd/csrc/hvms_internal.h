@@ -54,6 +54,39 @@ hipError_t launch_block_sort(int R, int NT, bool pairs, const int32_t *kin, cons
 hipError_t launch_gather_u64(const int32_t *idx, const uint64_t *src, uint64_t *dst, int64_t n,
                              hipStream_t s);
 
+// radix.hip: plain sorts by digit passes.  Kinds: keys alone, lexicographic
+// (key, value) pairs, packed 64-bit keys (at kin / kout), keys with 64-bit
+// payloads (stable).
+enum { RADIX_KEYS = 0, RADIX_PAIRS = 1, RADIX_KEYS64 = 2, RADIX_BY_KEY = 3 };
+struct RadixMap {
+    uint32_t x, f;  // word ^ (sign & f) ^ x: unsigned order
+};
+struct RadixArgs {
+    int64_t n, tiles;
+    int per_log2;           // tiles of a chunk
+    uint32_t *k[4], *v[4];
+    uint64_t *p[4];
+    void *ctl, *info;
+    uint32_t *totals;       // [digit]
+    uint32_t *counts;       // [chunk][digit]
+    uint32_t *rows;         // [tile][digit]: keys of the chunk's tiles before
+    int chunks;
+    RadixMap map;
+    uint32_t fl;
+};
+struct RadixIO {
+    const void *kin, *vin;
+    void *kout, *vout;
+    const uint64_t *pin;
+    uint64_t *pout;
+};
+struct RadixLayout {
+    int64_t a_k, a_v, b_k, b_v, a_p, ctl, totals, info, counts, rows, total;
+};
+RadixLayout radix_layout(int kind, int64_t n);
+hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap km,
+                        hipStream_t s);
+
 // merge.hip
 bool merge_tile_supported(int tm, bool pairs);
 hipError_t launch_pass_corank(bool pairs, const int32_t *kin, const int32_t *vin, int64_t n,

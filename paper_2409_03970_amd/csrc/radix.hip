@@ -1,0 +1,971 @@
+// Plain sorts by stable digit passes (least significant digit first): the
+// library's own choice where the caller asks for no merge shape (the sizes stand at
+// radix_route in abi.hip).
+//
+// A merge sort of 2^28 keys makes seven four-way trips through HBM with two
+// LDS merge levels in each; four passes over 8-bit digits read the keys twice
+// and write them once each, whatever their distribution, and need no co-rank
+// search.  Elements are compared by their mapped words: the key map of the
+// sort turned into unsigned order, applied by the first pass as it reads and
+// undone by the last as it writes.
+//
+// One pass is three launches:
+//   count    digit histogram of every chunk of tiles (one workgroup each; LDS
+//            atomics on 8 interleaved copies, so that equal digits in a wave
+//            meet 8 counters), and before each tile the chunk's counts so far;
+//   scan     exclusive prefix of every digit's counts over the chunks, and
+//            the digits' totals;
+//   scatter  a wave ranks 64 keys at a time: eight ballots give each lane the
+//            mask of lanes with its digit, a counter per wave and digit
+//            carries the rank on.  The tile is brought into digit order in
+//            LDS and written out in runs.
+// No workgroup waits for another.
+//
+// What bounds a pass (2^28 uniform keys): the count reads 1.07 GB in 0.27 ms
+// (4.0 TB/s, a read-only kernel's rate here).  The scatter takes 0.61 ms for
+// 2.15 GB: with its ranks left out and its writes made linear it would take
+// 0.39, with the writes alone linear 0.52, so both the partial cache lines at
+// the ends of the runs and the 55 VALU operations per key (32 of them the
+// ballots) show.  Run ends are why the tile is as large as two workgroups
+// per CU allow (16,384 keys, runs of 64: 0.665 against 0.79 ms at 8,192),
+// and why the tiles are dealt so that an XCD's workgroups walk one contiguous
+// range together: the line that two tiles' runs share is completed in that
+// XCD's L2 by a neighbouring workgroup (0.61 against 0.665 ms with a
+// contiguous range per workgroup).  Writing complete lines only, with the
+// rest of each run held back in LDS for the next tile, was no faster (0.685:
+// the branch per key and a third barrier cost what the lines saved), nor was
+// loading the next tile's keys ahead (registers spill at 128).
+//
+// The first count also finds which bits vary and whether the input is
+// already in order (or in reverse order).  From that one workgroup of the
+// first scan launch makes the plan of the sort: passes over constant digits
+// are skipped and presorted input is copied (sorted 2^28 keys 0.83 ms).  A
+// pair sort whose values ascend in the input skips its value digits, since
+// stable passes over the key alone then give the lexicographic order.
+// Skipped launches return at once; nothing is read back by the host.
+#include "common.h"
+#include "hvms_internal.h"
+
+namespace hvms {
+
+namespace {
+
+constexpr int RADIX = 256;
+constexpr int COUNT_NT = 512;
+constexpr int MAX_CHUNKS = 512;
+constexpr int COPIES = 8;  // interleaved histogram copies of the count kernel
+
+// buffers of a sort; the steps alternate between them
+enum { B_IN = 0, B_A = 1, B_B = 2, B_OUT = 3 };
+enum { STEP_SKIP = 0, STEP_SCATTER = 1, STEP_COPY = 2, STEP_REVERSE = 3 };
+
+struct Step {
+    uint32_t mode, src, dst, first, last;
+};
+
+struct Ctl {
+    Step step[8];
+};
+
+// The step of a pass, in scalar registers.
+__device__ __forceinline__ Step step_of(const void *ctl, int pass)
+{
+    const uint32_t *q = (const uint32_t *)&((const Ctl *)ctl)->step[pass];
+    Step s;
+    s.mode = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[0]);
+    s.src = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[1]);
+    s.dst = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[2]);
+    s.first = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[3]);
+    s.last = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[4]);
+    return s;
+}
+
+// What one chunk's count says about the input's order (flag set = not so).
+enum { NOT_ASCENDING = 1, NOT_DESCENDING = 2, VALUES_NOT_ASCENDING = 4 };
+struct ChunkInfo {
+    uint32_t and0, or0, and1, or1, flags, pad[3];
+};
+
+__device__ __forceinline__ uint32_t map_key(uint32_t v, RadixMap m)
+{
+    return v ^ ((uint32_t)((int32_t)v >> 31) & m.f) ^ m.x;
+}
+__device__ __forceinline__ uint32_t unmap_key(uint32_t u, RadixMap m)
+{
+    const uint32_t v = u ^ m.x;
+    return v ^ ((uint32_t)((int32_t)v >> 31) & m.f);
+}
+
+// An element: hi is the key (or the high word of a 64-bit key), lo the value
+// (or the low word); keys alone leave lo unused.
+struct Elem {
+    uint32_t hi, lo;
+};
+
+template <int KIND> __device__ __forceinline__ Elem map_elem2(Elem e, const RadixArgs &a)
+{
+    Elem r = e;
+    if constexpr (KIND == RADIX_KEYS64) {
+        const uint32_t s = (uint32_t)((int32_t)e.hi >> 31);
+        r.hi = e.hi ^ (s & a.map.f) ^ a.map.x;
+        r.lo = e.lo ^ (s & a.fl);
+    } else {
+        r.hi = map_key(e.hi, a.map);
+        if constexpr (KIND == RADIX_PAIRS)
+            r.lo = e.lo ^ 0x80000000u;
+    }
+    return r;
+}
+template <int KIND> __device__ __forceinline__ Elem unmap_elem2(Elem e, const RadixArgs &a)
+{
+    Elem r = e;
+    if constexpr (KIND == RADIX_KEYS64) {
+        const uint32_t v = e.hi ^ a.map.x;
+        const uint32_t s = (uint32_t)((int32_t)v >> 31);
+        r.hi = v ^ (s & a.map.f);
+        r.lo = e.lo ^ (s & a.fl);
+    } else {
+        r.hi = unmap_key(e.hi, a.map);
+        if constexpr (KIND == RADIX_PAIRS)
+            r.lo = e.lo ^ 0x80000000u;
+    }
+    return r;
+}
+
+// Element i of buffer b as stored (the 64-bit kind's caller arrays are
+// packed; its intermediate buffers are two word arrays).
+template <int KIND> __device__ __forceinline__ Elem load_raw(const RadixArgs &a, int b, int64_t i)
+{
+    Elem e{0, 0};
+    if constexpr (KIND == RADIX_KEYS64) {
+        if (b == B_IN || b == B_OUT) {
+            const uint2 q = ((const uint2 *)a.k[b])[i];
+            e.lo = q.x;
+            e.hi = q.y;
+            return e;
+        }
+    }
+    e.hi = a.k[b][i];
+    if constexpr (KIND == RADIX_PAIRS || KIND == RADIX_KEYS64)
+        e.lo = a.v[b][i];
+    return e;
+}
+template <int KIND>
+__device__ __forceinline__ void store_raw(const RadixArgs &a, int b, int64_t i, Elem e)
+{
+    if constexpr (KIND == RADIX_KEYS64) {
+        if (b == B_IN || b == B_OUT) {
+            ((uint2 *)a.k[b])[i] = make_uint2(e.lo, e.hi);
+            return;
+        }
+    }
+    a.k[b][i] = e.hi;
+    if constexpr (KIND == RADIX_PAIRS || KIND == RADIX_KEYS64)
+        a.v[b][i] = e.lo;
+}
+
+// ------------------------------------------------------------------- count
+
+__device__ __forceinline__ uint32_t wave_and(uint32_t x)
+{
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2)
+        x &= (uint32_t)__shfl_xor((int)x, d);
+    return x;
+}
+__device__ __forceinline__ uint32_t wave_or(uint32_t x)
+{
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2)
+        x |= (uint32_t)__shfl_xor((int)x, d);
+    return x;
+}
+
+// Digit d of the workgroup's histogram so far (d < 256).
+__device__ __forceinline__ uint32_t hist_sum(const uint32_t *hist, int d)
+{
+    uint32_t s = 0;
+    const uint4 *q = (const uint4 *)(hist + d * COPIES);
+#pragma unroll
+    for (int c = 0; c < COPIES / 4; ++c)
+        s += q[c].x + q[c].y + q[c].z + q[c].w;
+    return s;
+}
+
+// Pass 0: the histogram of digit 0 and what the plan needs to know.
+template <int KIND, int T>
+__global__ __launch_bounds__(COUNT_NT) void radix_count_first(RadixArgs a)
+{
+    __shared__ __align__(16) uint32_t hist[RADIX * COPIES];
+    __shared__ ChunkInfo part[COUNT_NT / 64];
+    for (int i = threadIdx.x; i < RADIX * COPIES; i += COUNT_NT)
+        hist[i] = 0;
+    const int lane = lane_id();
+    ChunkInfo f{~0u, 0u, ~0u, 0u, 0u, {0, 0, 0}};
+    // rows of 64 x UN consecutive elements per wave; lane l of row r holds
+    // element 64 r + l, and the next element comes from the next lane
+    constexpr int UN = KIND == RADIX_KEYS ? 8 : 4;
+    constexpr int STEP = COUNT_NT * UN;
+    const int64_t t0 = (int64_t)blockIdx.x << a.per_log2;
+    const int64_t t1 = min(t0 + ((int64_t)1 << a.per_log2), a.tiles);
+    for (int64_t tile = t0; tile < t1; ++tile) {
+        __syncthreads();
+        if (threadIdx.x < RADIX)
+            a.rows[tile * RADIX + threadIdx.x] = hist_sum(hist, threadIdx.x);
+        __syncthreads();
+        const int64_t hi = (tile + 1) * T < a.n ? (tile + 1) * T : a.n;
+        for (int64_t base = tile * T + (int64_t)(threadIdx.x / 64) * (64 * UN); base < hi;
+             base += STEP) {
+            Elem e[UN + 1];
+#pragma unroll
+            for (int r = 0; r <= UN; ++r) {
+                const int64_t i = base + r * 64 + (r < UN ? lane : 0);
+                e[r] = load_raw<KIND>(a, B_IN, i < a.n ? i : a.n - 1);
+            }
+#pragma unroll
+            for (int r = 0; r <= UN; ++r)
+                e[r] = map_elem2<KIND>(e[r], a);
+#pragma unroll
+            for (int r = 0; r < UN; ++r) {
+                const int64_t i = base + r * 64 + lane;
+                // the element after this one: the next lane's, or the next row's first
+                Elem nx;
+                nx.hi = (uint32_t)__shfl_down((int)e[r].hi, 1);
+                const uint32_t nh = (uint32_t)__builtin_amdgcn_readfirstlane((int)e[r + 1].hi);
+                nx.hi = lane == 63 ? nh : nx.hi;
+                bool gt = e[r].hi > nx.hi, lt = e[r].hi < nx.hi;
+                if constexpr (KIND == RADIX_PAIRS || KIND == RADIX_KEYS64) {
+                    nx.lo = (uint32_t)__shfl_down((int)e[r].lo, 1);
+                    const uint32_t nl = (uint32_t)__builtin_amdgcn_readfirstlane((int)e[r + 1].lo);
+                    nx.lo = lane == 63 ? nl : nx.lo;
+                    const bool eq = e[r].hi == nx.hi;
+                    gt = gt || (eq && e[r].lo > nx.lo);
+                    lt = lt || (eq && e[r].lo < nx.lo);
+                    if (KIND == RADIX_PAIRS && i + 1 < a.n && e[r].lo > nx.lo)
+                        f.flags |= VALUES_NOT_ASCENDING;
+                }
+                // a stable sort may reverse only where no two keys are equal
+                if constexpr (KIND == RADIX_BY_KEY)
+                    lt = e[r].hi <= nx.hi;
+                if (i + 1 < a.n)
+                    f.flags |= (gt ? NOT_ASCENDING : 0) | (lt ? NOT_DESCENDING : 0);
+                if (i < hi) {
+                    f.and1 &= e[r].hi;
+                    f.or1 |= e[r].hi;
+                    if constexpr (KIND == RADIX_PAIRS || KIND == RADIX_KEYS64) {
+                        f.and0 &= e[r].lo;
+                        f.or0 |= e[r].lo;
+                    }
+                    const uint32_t w =
+                        (KIND == RADIX_PAIRS || KIND == RADIX_KEYS64) ? e[r].lo : e[r].hi;
+                    atomicAdd(&hist[(w & 255) * COPIES + (lane & (COPIES - 1))], 1u);
+                }
+            }
+        }
+    }
+    f.and0 = wave_and(f.and0);
+    f.or0 = wave_or(f.or0);
+    f.and1 = wave_and(f.and1);
+    f.or1 = wave_or(f.or1);
+    f.flags = wave_or(f.flags);
+    if (lane == 0)
+        part[threadIdx.x / 64] = f;
+    __syncthreads();
+    if (threadIdx.x < RADIX)
+        a.counts[(int64_t)blockIdx.x * RADIX + threadIdx.x] = hist_sum(hist, threadIdx.x);
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < COUNT_NT / 64; ++w) {
+            f.and0 &= part[w].and0;
+            f.or0 |= part[w].or0;
+            f.and1 &= part[w].and1;
+            f.or1 |= part[w].or1;
+            f.flags |= part[w].flags;
+        }
+        ((ChunkInfo *)a.info)[blockIdx.x] = f;
+    }
+}
+
+// Later passes: the histogram of one digit of one word array.
+template <int KIND, int T>
+__global__ __launch_bounds__(COUNT_NT) void radix_count(RadixArgs a, int pass)
+{
+    const Step st = step_of(a.ctl, pass);
+    if (st.mode != STEP_SCATTER)
+        return;
+    __shared__ __align__(16) uint32_t hist[RADIX * COPIES];
+    for (int i = threadIdx.x; i < RADIX * COPIES; i += COUNT_NT)
+        hist[i] = 0;
+    const int copy = threadIdx.x & (COPIES - 1);
+    constexpr bool TWO = KIND == RADIX_PAIRS || KIND == RADIX_KEYS64;
+    const bool low = TWO && pass < 4;
+    const int shift = 8 * (pass & 3);
+    const uint32_t *p = low ? a.v[st.src] : a.k[st.src];
+    // st.first: the caller's array, unmapped (the passes before were skipped)
+    const bool wide = !st.first && ((uintptr_t)p & 15) == 0;
+    const int64_t t0 = (int64_t)blockIdx.x << a.per_log2;
+    const int64_t t1 = min(t0 + ((int64_t)1 << a.per_log2), a.tiles);
+    for (int64_t tile = t0; tile < t1; ++tile) {
+        const int64_t lo = tile * T, hi = lo + T < a.n ? lo + T : a.n;
+        constexpr int UN = T / (4 * COUNT_NT);
+        uint4 q[UN];
+        const bool full = wide && hi - lo == T;
+        if (full) {
+#pragma unroll
+            for (int u = 0; u < UN; ++u)
+                q[u] = *(const uint4 *)(p + lo + (u * COUNT_NT + threadIdx.x) * 4);
+        }
+        __syncthreads();
+        if (threadIdx.x < RADIX)
+            a.rows[tile * RADIX + threadIdx.x] = hist_sum(hist, threadIdx.x);
+        __syncthreads();
+        if (full) {
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                atomicAdd(&hist[((q[u].x >> shift) & 255) * COPIES + copy], 1u);
+                atomicAdd(&hist[((q[u].y >> shift) & 255) * COPIES + copy], 1u);
+                atomicAdd(&hist[((q[u].z >> shift) & 255) * COPIES + copy], 1u);
+                atomicAdd(&hist[((q[u].w >> shift) & 255) * COPIES + copy], 1u);
+            }
+        } else {
+            for (int64_t i = lo + threadIdx.x; i < hi; i += COUNT_NT) {
+                uint32_t w;
+                if (st.first) {
+                    const Elem e = map_elem2<KIND>(load_raw<KIND>(a, st.src, i), a);
+                    w = low ? e.lo : e.hi;
+                } else {
+                    w = p[i];
+                }
+                atomicAdd(&hist[((w >> shift) & 255) * COPIES + copy], 1u);
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < RADIX)
+        a.counts[(int64_t)blockIdx.x * RADIX + threadIdx.x] = hist_sum(hist, threadIdx.x);
+}
+
+// -------------------------------------------------------------------- scan
+
+// Inclusive prefix sum over the lanes of a wave (row shifts, then the row
+// sums broadcast to the following rows).
+__device__ __forceinline__ uint32_t wave_inclusive(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);  // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);  // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);  // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);  // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false); // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false); // row_bcast:31
+    return x;
+}
+
+// The steps of the sort from what the chunks found (one workgroup).
+__device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64, bool inplace)
+{
+    __shared__ ChunkInfo part[8];
+    ChunkInfo f{~0u, 0u, ~0u, 0u, 0u, {0, 0, 0}};
+    const ChunkInfo *info = (const ChunkInfo *)a.info;
+    for (int c = threadIdx.x; c < a.chunks; c += 512) {
+        const ChunkInfo g = info[c];
+        f.and0 &= g.and0;
+        f.or0 |= g.or0;
+        f.and1 &= g.and1;
+        f.or1 |= g.or1;
+        f.flags |= g.flags;
+    }
+    f.and0 = wave_and(f.and0);
+    f.or0 = wave_or(f.or0);
+    f.and1 = wave_and(f.and1);
+    f.or1 = wave_or(f.or1);
+    f.flags = wave_or(f.flags);
+    if (lane_id() == 0)
+        part[threadIdx.x / 64] = f;
+    __syncthreads();
+    if (threadIdx.x != 0)
+        return;
+    for (int w = 1; w < 8; ++w) {
+        f.and0 &= part[w].and0;
+        f.or0 |= part[w].or0;
+        f.and1 &= part[w].and1;
+        f.or1 |= part[w].or1;
+        f.flags |= part[w].flags;
+    }
+    Ctl *ctl = (Ctl *)a.ctl;
+    uint32_t mode[8];
+    int steps = 0;
+    const bool ascending = !(f.flags & NOT_ASCENDING);
+    const bool descending = !(f.flags & NOT_DESCENDING);
+    for (int p = 0; p < passes; ++p)
+        mode[p] = STEP_SKIP;
+    if (ascending) {
+        mode[passes - 1] = STEP_COPY;
+        steps = 1;
+    } else if (descending) {
+        mode[passes - 1] = STEP_REVERSE;
+        steps = 1;
+        if (inplace) {  // through the scratch, since both ends move
+            mode[passes - 2] = STEP_REVERSE;
+            mode[passes - 1] = STEP_COPY;
+            steps = 2;
+        }
+    } else {
+        // a set bit: this bit differs between two elements
+        const uint32_t var0 = f.and0 ^ f.or0, var1 = f.and1 ^ f.or1;
+        for (int p = 0; p < passes; ++p) {
+            const uint32_t var = (two && p < 4) ? var0 : var1;
+            bool need = ((var >> (8 * (p & 3))) & 255) != 0;
+            if (two && !keys64 && p < 4 && !(f.flags & VALUES_NOT_ASCENDING))
+                need = false;
+            if (need) {
+                mode[p] = STEP_SCATTER;
+                ++steps;
+            }
+        }
+        // In place, the first step must not write the array it reads: with a
+        // step count that would make it, one skipped pass copies instead.
+        const bool clash = keys64 ? steps == 1 : (steps & 1) != 0;
+        if (inplace && clash) {
+            for (int p = 0; p < passes; ++p)
+                if (mode[p] == STEP_SKIP) {
+                    mode[p] = STEP_COPY;
+                    ++steps;
+                    break;
+                }
+        }
+    }
+    int j = 0;
+    uint32_t cur = B_IN;
+    for (int p = 0; p < passes; ++p) {
+        Step s{mode[p], 0, 0, 0, 0};
+        if (mode[p] != STEP_SKIP) {
+            s.first = j == 0;
+            s.last = j == steps - 1;
+            s.src = cur;
+            if (s.last)
+                s.dst = B_OUT;
+            else if (keys64)
+                s.dst = (j & 1) ? B_B : B_A;
+            else
+                s.dst = ((steps - 1 - j) & 1) ? B_A : B_OUT;
+            cur = s.dst;
+            ++j;
+        }
+        ctl->step[p] = s;
+    }
+}
+
+// Workgroup g: the exclusive prefixes of the counts of digits 16 g .. 16 g +
+// 15 over the chunks, in place, and the digits' totals; thread t walks digit
+// t mod 16 over the (t / 16)th part of the chunks.  In pass 0 one more
+// workgroup makes the plan.
+__global__ __launch_bounds__(512) void radix_scan(RadixArgs a, int pass, int passes, int two,
+                                                  int keys64, int inplace)
+{
+    if (blockIdx.x == RADIX / 16) {
+        make_plan(a, passes, two != 0, keys64 != 0, inplace != 0);
+        return;
+    }
+    if (pass > 0 && step_of(a.ctl, pass).mode != STEP_SCATTER)
+        return;
+    __shared__ uint32_t sum[32][16];
+    const int d = threadIdx.x & 15, q = threadIdx.x >> 4;
+    constexpr int PER = MAX_CHUNKS / 32;
+    uint32_t *col = a.counts + blockIdx.x * 16 + d;
+    uint32_t v[PER], s = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int c = q * PER + i;
+        v[i] = c < a.chunks ? col[c * RADIX] : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        s += v[i];
+    sum[q][d] = s;
+    __syncthreads();
+    uint32_t ex = 0, all = 0;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        ex += i < q ? sum[i][d] : 0;
+        all += sum[i][d];
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int c = q * PER + i;
+        if (c < a.chunks)
+            col[c * RADIX] = ex;
+        ex += v[i];
+    }
+    if (q == 0)
+        a.totals[blockIdx.x * 16 + d] = all;
+}
+
+// ----------------------------------------------------------------- scatter
+
+// Mask of the lanes whose digit (8 bits at `shift`) equals this lane's.
+__device__ __forceinline__ void match_digit(uint32_t d, uint32_t &lo, uint32_t &hi)
+{
+    lo = ~0u;
+    hi = ~0u;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        // all ones where the bit is set; hidden from the optimizer, which
+        // would otherwise compute the sign a second time by a shift
+        int32_t t = __builtin_amdgcn_sbfe((int)d, b, 1);
+        asm("" : "+v"(t));
+        const uint64_t set = __builtin_amdgcn_ballot_w64(t != 0);
+        // mask & ~(set ^ t): lanes whose bit equals this lane's
+        lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)set, (uint32_t)t, 0x90);
+        hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(set >> 32), (uint32_t)t, 0x90);
+    }
+}
+
+template <int NT, int KIND>
+__device__ __forceinline__ void copy_step(const RadixArgs &a, const Step &st)
+{
+    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < a.n; i += (int64_t)gridDim.x * NT) {
+        const int64_t o = st.mode == STEP_REVERSE ? a.n - 1 - i : i;
+        Elem e = load_raw<KIND>(a, st.src, i);
+        if (st.first)
+            e = map_elem2<KIND>(e, a);
+        if (st.last)
+            e = unmap_elem2<KIND>(e, a);
+        store_raw<KIND>(a, st.dst, o, e);
+        if constexpr (KIND == RADIX_BY_KEY)
+            a.p[st.dst][o] = a.p[st.src][i];
+    }
+}
+
+template <int NT, int K, int KIND, int WAVES>
+__global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass)
+{
+    constexpr int T = NT * K;
+    constexpr int NW = NT / 64;
+    constexpr int B = 8;  // positions written out at a time
+    constexpr bool TWO = KIND == RADIX_PAIRS || KIND == RADIX_KEYS64;
+    // 64-bit payloads are exchanged as such, 32-bit words one after the other
+    constexpr int XB = KIND == RADIX_BY_KEY ? 8 : 4;
+    static_assert(T <= 65536 && K % B == 0, "16-bit tile positions");
+    __shared__ __align__(16) unsigned char xraw[T * XB];
+    __shared__ __align__(16) uint16_t cnt[NW][RADIX];  // keys of each digit per wave
+    __shared__ __align__(16) uint16_t off[NW][RADIX];  // tile position of a wave's first such key
+    __shared__ __align__(16) uint32_t gbase[RADIX];    // output index minus tile position
+    __shared__ __align__(16) uint32_t gpre[RADIX];     // output index of the tile's first such key
+    uint32_t *xch = (uint32_t *)xraw;
+
+    const Step st = step_of(a.ctl, pass);
+    if (st.mode == STEP_SKIP)
+        return;
+    if (st.mode != STEP_SCATTER) {
+        copy_step<NT, KIND>(a, st);
+        return;
+    }
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int shift = 8 * (pass & 3);
+    const bool low = TWO && pass < 4;  // the digit's word
+    const bool packed_in = KIND == RADIX_KEYS64 && st.src == B_IN;
+    const bool packed_out = KIND == RADIX_KEYS64 && st.dst == B_OUT;
+    // w: the array of the word that holds the digit, s: the other word's
+    const uint32_t *wsrc = low && !packed_in ? a.v[st.src] : a.k[st.src];
+    const uint32_t *ssrc = low || packed_in ? a.k[st.src] : a.v[st.src];
+    uint32_t *wdst = low ? a.v[st.dst] : a.k[st.dst];
+    uint32_t *sdst = low ? a.k[st.dst] : a.v[st.dst];
+
+    // thread t < 256: where digit t's region of the output starts
+    uint32_t region = 0;
+    if (wave == 0) {
+        const uint4 t = *(const uint4 *)(a.totals + 4 * lane);
+        const uint32_t s = t.x + t.y + t.z + t.w;
+        const uint32_t ex = wave_inclusive(s) - s;
+        *(uint4 *)&gpre[4 * lane] =
+            make_uint4(ex, ex + t.x, ex + t.x + t.y, ex + t.x + t.y + t.z);
+    }
+    __syncthreads();
+    if (tid < RADIX)
+        region = gpre[tid];
+
+    // An XCD's workgroups (every eighth one) walk one contiguous range of
+    // tiles together, so that the lines two neighbouring tiles share are
+    // completed in that XCD's L2.
+    const int slots = (int)gridDim.x >> 3;
+    const int64_t xcd = blockIdx.x & 7;
+    const int64_t tile1 = (xcd + 1) * a.tiles >> 3;
+    int64_t tile = (xcd * a.tiles >> 3) + (blockIdx.x >> 3);
+    // Loads of a tile's words through buffer resources: they end at the
+    // array's last element (zeros past it) and take one lane offset and
+    // constant row offsets.  hi: which word of a packed array.
+    const auto load_words = [&](const uint32_t *p, bool packed, bool hi, int64_t base, int e0,
+                                uint32_t(&x)[K]) {
+        const uint32_t valid = a.n - base < T ? (uint32_t)(a.n - base) : (uint32_t)T;
+        if (packed) {
+            const __amdgpu_buffer_rsrc_t r = raw_rsrc(p + 2 * base, 8u * valid);
+            const int h = hi ? 4 : 0;
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                x[k] = __builtin_amdgcn_raw_buffer_load_b32(r, 8 * e0 + 8 * 64 * k, h, 0);
+        } else {
+            // streamed (nt): the L2 is for the lines being written
+            const __amdgpu_buffer_rsrc_t r = raw_rsrc(p + base, 4u * valid);
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                x[k] = __builtin_amdgcn_raw_buffer_load_b32(r, 4 * e0 + 4 * 64 * k, 0, 2);
+        }
+    };
+    uint32_t w[K];
+    for (; tile < tile1; tile += slots) {
+        const int64_t base = tile * T;
+        const int cnt_valid = a.n - base < T ? (int)(a.n - base) : T;
+        uint32_t first = region;
+        if (tid < RADIX)
+            first += a.rows[tile * RADIX + tid] + a.counts[(tile >> a.per_log2) * RADIX + tid];
+        int t0 = tid;
+        asm("" : "+v"(t0));  // keeps the row offsets out of registers held across tiles
+        const int e0 = wave * (64 * K) + (t0 & 63);
+        load_words(wsrc, packed_in, !low, base, e0, w);
+        if (st.first) {
+            if (KIND == RADIX_KEYS64 && low) {  // the low word's map follows the sign
+                uint32_t h[K];
+                load_words(ssrc, packed_in, true, base, e0, h);
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    w[k] = map_elem2<KIND>(Elem{h[k], w[k]}, a).lo;
+            } else {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const Elem e = map_elem2<KIND>(Elem{w[k], w[k]}, a);
+                    w[k] = low ? e.lo : e.hi;
+                }
+            }
+        }
+        // pads take the last positions of the tile: the largest digit,
+        // after every real element in tile order
+        if (cnt_valid != T) {
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (e0 + k * 64 >= cnt_valid)
+                    w[k] = ~0u;
+        }
+
+        // ranks among the wave's keys of the same digit, two to a register
+        *(uint2 *)&cnt[wave][4 * lane] = make_uint2(0, 0);
+        uint32_t pos[K / 2];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint32_t d = (w[k] >> shift) & 255;
+            uint32_t mlo, mhi;
+            match_digit(d, mlo, mhi);
+            const uint32_t before =
+                __builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(mlo, 0));
+            const uint32_t all = __popc(mlo) + __popc(mhi);
+            const uint32_t c = cnt[wave][d];
+            if (k & 1)
+                pos[k / 2] |= (c + before) << 16;
+            else
+                pos[k / 2] = c + before;
+            if (before == 0)
+                cnt[wave][d] = (uint16_t)(c + all);
+            // the next row's reads follow this row's writes of other lanes:
+            // one wave's LDS operations complete in order, so only the
+            // compiler has to keep them so
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_sched_barrier(0);  // one row's masks at a time
+        }
+        if (tid < RADIX)
+            gpre[tid] = first;
+        __syncthreads();
+
+        // every wave adds up the waves' counts itself: 4 digits per lane
+        {
+            uint32_t t[4] = {0, 0, 0, 0}, mine[4] = {0, 0, 0, 0};
+#pragma unroll 4
+            for (int v = 0; v < NW; ++v) {
+                const uint2 q = *(const uint2 *)&cnt[v][4 * lane];
+                if (v == wave) {
+                    mine[0] = t[0];
+                    mine[1] = t[1];
+                    mine[2] = t[2];
+                    mine[3] = t[3];
+                }
+                t[0] += q.x & 0xffff;
+                t[1] += q.x >> 16;
+                t[2] += q.y & 0xffff;
+                t[3] += q.y >> 16;
+            }
+            const uint32_t sum = t[0] + t[1] + t[2] + t[3];
+            uint32_t ex = wave_inclusive(sum) - sum;
+            if (wave == 0) {
+                uint4 g = *(const uint4 *)&gpre[4 * lane];
+                g.x -= ex;
+                g.y -= ex + t[0];
+                g.z -= ex + t[0] + t[1];
+                g.w -= ex + t[0] + t[1] + t[2];
+                *(uint4 *)&gbase[4 * lane] = g;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                mine[j] += ex;
+                ex += t[j];
+            }
+            *(uint2 *)&off[wave][4 * lane] =
+                make_uint2(mine[0] | (mine[1] << 16), mine[2] | (mine[3] << 16));
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            asm("" : "+v"(w[k]));  // the digit is cheaper taken again than kept
+            const uint32_t o = off[wave][(w[k] >> shift) & 255];
+            pos[k / 2] += k & 1 ? o << 16 : o;
+            xch[k & 1 ? pos[k / 2] >> 16 : (pos[k / 2] & 0xffff)] = w[k];
+        }
+        // the other words travel while the first are written out
+        uint32_t s[TWO ? K : 1];
+        uint64_t q[KIND == RADIX_BY_KEY ? K : 1];
+        if constexpr (TWO)
+            load_words(ssrc, packed_in, low, base, e0, s);
+        if constexpr (KIND == RADIX_BY_KEY) {
+            const __amdgpu_buffer_rsrc_t rp =
+                raw_rsrc(a.p[st.src] + base, 8u * (uint32_t)cnt_valid);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(rp, 8 * e0 + 8 * 64 * k, 0, 0);
+                q[k] = ((uint64_t)(uint32_t)v[1] << 32) | (uint32_t)v[0];
+            }
+        }
+        __syncthreads();
+        // out in digit order; o: each position's output index
+        const bool full = cnt_valid == T;
+        uint32_t o[K];
+#pragma unroll
+        for (int i0 = 0; i0 < K; i0 += B) {
+#pragma unroll
+            for (int i = i0; i < i0 + B; ++i)
+                w[i] = xch[t0 + i * NT];
+#pragma unroll
+            for (int i = i0; i < i0 + B; ++i) {
+                o[i] = gbase[(w[i] >> shift) & 255] + (uint32_t)(t0 + i * NT);
+                if (!packed_out) {
+                    uint32_t v = w[i];
+                    if (st.last) {
+                        const Elem e = unmap_elem2<KIND>(Elem{v, v}, a);
+                        v = low ? e.lo : e.hi;
+                    }
+                    if (full || t0 + i * NT < cnt_valid)
+                        wdst[o[i]] = v;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (TWO) {
+            // a 64-bit key's low word is mapped by the sign: below, beside it
+            const bool pair_map = KIND == RADIX_KEYS64 && !low && st.first;
+            if (st.first && !pair_map) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const Elem e = map_elem2<KIND>(Elem{s[k], s[k]}, a);
+                    s[k] = low ? e.hi : e.lo;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                xch[k & 1 ? pos[k / 2] >> 16 : (pos[k / 2] & 0xffff)] = s[k];
+            __syncthreads();
+#pragma unroll
+            for (int i0 = 0; i0 < K; i0 += B) {
+#pragma unroll
+                for (int i = i0; i < i0 + B; ++i)
+                    s[i] = xch[t0 + i * NT];
+#pragma unroll
+                for (int i = i0; i < i0 + B; ++i) {
+                    if (!(full || t0 + i * NT < cnt_valid))
+                        continue;
+                    if (pair_map)
+                        s[i] = map_elem2<KIND>(
+                                   Elem{unmap_elem2<KIND>(Elem{w[i], 0}, a).hi, s[i]}, a)
+                                   .lo;
+                    if (packed_out) {
+                        const Elem e =
+                            unmap_elem2<KIND>(Elem{low ? s[i] : w[i], low ? w[i] : s[i]}, a);
+                        ((uint2 *)a.k[B_OUT])[o[i]] = make_uint2(e.lo, e.hi);
+                    } else {
+                        uint32_t v = s[i];
+                        if (st.last) {
+                            const Elem e = unmap_elem2<KIND>(Elem{v, v}, a);
+                            v = low ? e.hi : e.lo;
+                        }
+                        sdst[o[i]] = v;
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if constexpr (KIND == RADIX_BY_KEY) {
+            uint64_t *pdst = a.p[st.dst];
+            uint64_t *x8 = (uint64_t *)xraw;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                x8[k & 1 ? pos[k / 2] >> 16 : (pos[k / 2] & 0xffff)] = q[k];
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < K; ++i)
+                if (full || t0 + i * NT < cnt_valid)
+                    pdst[o[i]] = x8[t0 + i * NT];
+        }
+    }
+}
+
+constexpr int64_t align256(int64_t b) { return (b + 255) & ~(int64_t)255; }
+
+
+// Workgroup shapes of the scatter kernel; the layout of the workspace and the
+// launches both follow from shape_of, so they cannot disagree on the tile.
+struct Shape {
+    int nt, k;
+};
+constexpr Shape SHAPES[] = {{256, 8}, {512, 16}, {512, 32}};
+
+// Small sorts take small tiles (more workgroups than 8,192-key tiles give:
+// 2^20 keys 66 against 71 us, 2^22 keys 96 and 97), keys alone large ones once
+// the runs go to HBM (2^26 keys 0.78 against 0.80 ms, 2^28 keys 3.78 against
+// 3.40).  Two words a key at K = 32 would spill.
+int shape_of(int kind, int64_t n)
+{
+    if (n < ((int64_t)1 << 22))
+        return 0;
+    return kind == RADIX_KEYS && n >= ((int64_t)1 << 27) ? 2 : 1;
+}
+int tile_of(int kind, int64_t n)
+{
+    const Shape s = SHAPES[shape_of(kind, n)];
+    return s.nt * s.k;
+}
+
+// log2 of the tiles per chunk: at most MAX_CHUNKS chunks, half as many where
+// there are few tiles (whose counts then fit the fixed scratch of the
+// allocation-free sort beside 2^22 keys).
+int chunk_log2(int64_t tiles)
+{
+    const int64_t most = tiles > 2 * MAX_CHUNKS ? MAX_CHUNKS : MAX_CHUNKS / 2;
+    int l = 0;
+    while ((tiles + ((int64_t)1 << l) - 1) >> l > most)
+        ++l;
+    return l;
+}
+
+}  // namespace
+
+RadixLayout radix_layout(int kind, int64_t n)
+{
+    RadixLayout w{};
+    int64_t off = 0;
+    w.a_k = off;
+    off += align256(n * 4);
+    if (kind == RADIX_PAIRS || kind == RADIX_KEYS64) {
+        w.a_v = off;
+        off += align256(n * 4);
+    }
+    if (kind == RADIX_KEYS64) {
+        w.b_k = off;
+        off += align256(n * 4);
+        w.b_v = off;
+        off += align256(n * 4);
+    }
+    if (kind == RADIX_BY_KEY) {
+        w.a_p = off;
+        off += align256(n * 8);
+    }
+    const int64_t tiles = (n + tile_of(kind, n) - 1) / tile_of(kind, n);
+    const int l = chunk_log2(tiles);
+    const int64_t chunks = (tiles + ((int64_t)1 << l) - 1) >> l;
+    w.ctl = off;
+    off += align256(sizeof(Ctl));
+    w.totals = off;
+    off += align256(RADIX * 4);
+    w.info = off;
+    off += align256(chunks * (int64_t)sizeof(ChunkInfo));
+    w.counts = off;
+    off += align256(chunks * RADIX * 4);
+    w.rows = off;
+    off += align256(tiles * RADIX * 4);
+    w.total = off;
+    return w;
+}
+
+// WAVES: waves per SIMD the registers are kept to; WGS: workgroups per CU.
+template <int KIND, int SHAPE, int WAVES, int WGS>
+static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
+{
+    constexpr int NT = SHAPES[SHAPE].nt, K = SHAPES[SHAPE].k, T = NT * K;
+    constexpr bool two = KIND == RADIX_PAIRS || KIND == RADIX_KEYS64;
+    constexpr bool keys64 = KIND == RADIX_KEYS64;
+    constexpr int passes = two ? 8 : 4;
+    a.tiles = (a.n + T - 1) / T;
+    a.per_log2 = chunk_log2(a.tiles);
+    a.chunks = (int)((a.tiles + ((int64_t)1 << a.per_log2) - 1) >> a.per_log2);
+    const int64_t fit = (int64_t)device_cus() * WGS;
+    int64_t wg = a.tiles < fit ? a.tiles : fit;
+    wg = (wg + 7) & ~(int64_t)7;
+    const dim3 cgrid((unsigned)a.chunks), sgrid((unsigned)wg);
+    for (int p = 0; p < passes; ++p) {
+        if (p == 0)
+            hipLaunchKernelGGL((radix_count_first<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a);
+        else
+            hipLaunchKernelGGL((radix_count<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a, p);
+        hipLaunchKernelGGL(radix_scan, dim3(RADIX / 16 + (p == 0)), dim3(512), 0, s, a, p, passes,
+                           (int)two, (int)keys64, (int)inplace);
+        hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES>), sgrid, dim3(NT), 0, s, a, p);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap km,
+                        hipStream_t s)
+{
+    const RadixLayout w = radix_layout(kind, n);
+    char *base = (char *)ws;
+    RadixArgs a{};
+    a.n = n;
+    a.k[B_IN] = (uint32_t *)io.kin;
+    a.v[B_IN] = (uint32_t *)io.vin;
+    a.p[B_IN] = (uint64_t *)io.pin;
+    a.k[B_OUT] = (uint32_t *)io.kout;
+    a.v[B_OUT] = (uint32_t *)io.vout;
+    a.p[B_OUT] = io.pout;
+    a.k[B_A] = (uint32_t *)(base + w.a_k);
+    a.v[B_A] = (uint32_t *)(base + w.a_v);
+    a.p[B_A] = (uint64_t *)(base + w.a_p);
+    a.k[B_B] = (uint32_t *)(base + w.b_k);
+    a.v[B_B] = (uint32_t *)(base + w.b_v);
+    a.ctl = base + w.ctl;
+    a.totals = (uint32_t *)(base + w.totals);
+    a.info = base + w.info;
+    a.counts = (uint32_t *)(base + w.counts);
+    a.rows = (uint32_t *)(base + w.rows);
+    // signed order (after the key map) to unsigned order of the words
+    a.map.f = (uint32_t)km.fm;
+    a.map.x = (uint32_t)km.um ^ 0x80000000u;
+    a.fl = (uint32_t)km.fl;
+    const bool inplace = io.kin == io.kout || (io.vin && io.vin == io.vout);
+    const int shape = shape_of(kind, n);
+    switch (kind) {
+    case RADIX_KEYS:
+        return shape == 0   ? run_radix<RADIX_KEYS, 0, 6, 6>(a, inplace, s)
+               : shape == 1 ? run_radix<RADIX_KEYS, 1, 6, 3>(a, inplace, s)
+                            : run_radix<RADIX_KEYS, 2, 4, 2>(a, inplace, s);
+    case RADIX_PAIRS:
+        if (shape == 0)
+            break;
+        return run_radix<RADIX_PAIRS, 1, 4, 2>(a, inplace, s);
+    case RADIX_KEYS64:
+        if (shape == 0)
+            break;
+        return run_radix<RADIX_KEYS64, 1, 4, 2>(a, inplace, s);
+    case RADIX_BY_KEY:
+        return shape == 0 ? run_radix<RADIX_BY_KEY, 0, 4, 4>(a, inplace, s)
+                          : run_radix<RADIX_BY_KEY, 1, 4, 2>(a, inplace, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace hvms
