@@ -3,18 +3,18 @@
 // partition points of the parallel merge (Sec. 2.1); an exact bounded search
 // corrects every prediction, so sort results never depend on it.
 //
-// Kernels (plain VALU fp32; the model is far too small for matrix cores):
+// Kernels:
 //   forward      one thread per sample, parameters staged in LDS;
-//   backward     phase 1: one thread per sample computes its forward values
-//                and the per-sample factors of every gradient entry;
-//                phase 2: each workgroup sums a fixed chunk of samples for all
-//                1153 entries (+ the loss) in sample order;
-//                phase 3: one thread per entry sums the chunk partials in
-//                chunk order -- every sum has a fixed order, so reruns are
-//                bitwise identical;
-//   adam         one thread per parameter (Kingma and Ba 2015, Algorithm 1);
+//   gradient     forward and backward of 32 samples at a time on the fp32
+//                matrix cores (see cdf_grad_kernel), every workgroup leaving
+//                its sums over a fixed set of samples in a row of partials;
+//   reduce       one entry's partials added in a fixed order, in training
+//                followed at once by the entry's Adam step (Kingma and Ba
+//                2015, Algorithm 1).  Every sum has a fixed order, so reruns
+//                are bitwise identical;
 //   minibatch    sample positions from SplitMix64 (Steele, Lea, Flood 2014)
-//                on a counter, key -> x, position/m -> target.
+//                on a counter, key -> x, position/m -> target, drawn by the
+//                gradient kernel itself.
 #include "hvms.h"
 #include "hvms_internal.h"
 #include "mlp_common.h"
@@ -25,8 +25,9 @@ namespace {
 
 constexpr int H = 32;
 constexpr int NP = HVMS_CDF_PARAMS;  // 1153
-constexpr int NREC = 4 + 4 * H;      // per-sample record: x, dy, sq, pad, h1, dz1, h2, dz2
-constexpr int CHUNK = 128;           // samples per phase-2 workgroup
+constexpr int NREC = 4 + 4 * H;      // floats per sample the workspace is sized by
+constexpr int CHUNK = 128;           // samples a workgroup takes at a time (4 waves x 32)
+constexpr int GRAD_WGS = 256;        // rows of partials at most: one workgroup per CU
 
 __global__ __launch_bounds__(256) void cdf_forward_kernel(const float *__restrict__ p,
                                                           const float *__restrict__ x,
@@ -56,151 +57,225 @@ __global__ __launch_bounds__(256) void cdf_table_kernel(const float *__restrict_
         table[i] = cdf_eval(P, (float)i * (1.0f / kCdfTableSteps));
 }
 
-// Phase 1: rec[f * b + i] holds field f of sample i.
-__global__ __launch_bounds__(256) void cdf_bwd_samples_kernel(const float *__restrict__ p,
-                                                              const float *__restrict__ x,
-                                                              const float *__restrict__ tgt,
-                                                              float *__restrict__ rec, int64_t b)
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// The 32x32 matrix product's operands in a wave (v_mfma_f32_32x32x2_f32):
+// A[i][k] and B[k][j] sit in lane 32 k + i and 32 k + j, D[i][j] in register
+// r of lane 32 g + j with i = unit(r, g).  The sixteen k steps of a product
+// may take the units in any order, so step r takes units unit(r, 0) and
+// unit(r, 1): a product's result registers are then the next one's B operand
+// as they stand.
+__device__ __forceinline__ constexpr int unit(int r, int g) { return 8 * (r >> 2) + 4 * g + (r & 3); }
+
+// Sum over the 32 lanes of each half of the wave, in its last lane.
+__device__ __forceinline__ float half_sum(float v)
 {
-    __shared__ float P[NP];
-    for (int i = threadIdx.x; i < NP; i += blockDim.x)
-        P[i] = p[i];
+    const auto add = [](float x, int y) { return x + __builtin_bit_cast(float, y); };
+    const auto bits = [](float x) { return __builtin_bit_cast(int, x); };
+    v = add(v, __builtin_amdgcn_update_dpp(0, bits(v), 0x111, 0xF, 0xF, true));  // row_shr:1
+    v = add(v, __builtin_amdgcn_update_dpp(0, bits(v), 0x112, 0xF, 0xF, true));  // row_shr:2
+    v = add(v, __builtin_amdgcn_update_dpp(0, bits(v), 0x114, 0xF, 0xF, true));  // row_shr:4
+    v = add(v, __builtin_amdgcn_update_dpp(0, bits(v), 0x118, 0xF, 0xF, true));  // row_shr:8
+    v = add(v, __builtin_amdgcn_update_dpp(0, bits(v), 0x142, 0xA, 0xF, false)); // row_bcast:15
+    return v;
+}
+
+// Loss and gradient sums of a fixed share of the samples, one row of NP + 1
+// partials per workgroup.
+//
+// A wave takes 32 samples (lane 32 g + s: sample s): h1 in registers, then
+// z2 = W2 h1, dh1 = W2^T dz2 and dW2 += dz2 h1^T as 16 matrix steps each, in
+// fp32; only the last needs its operands turned (samples along k), through
+// LDS.  The other sums stay in the lanes until the end.  48 matrix steps of
+// 64 cycles bound a block of samples: 65,536 samples are two blocks per SIMD,
+// 2.6 us.  Before, the per-sample factors of every gradient entry went
+// through memory (34 MB for 65,536 samples), one workgroup per 128 samples
+// multiplied them on the VALU, and five workgroups added 512 rows of partials
+// one after the other: 478 us a training step, now 15 us (12.7 here, 3.9 in the
+// reduction; drawing the second block's samples during the first was no faster).
+//
+// TRAIN: the samples are a minibatch drawn here, position
+// i_k = SplitMix64(seed, step * 2^32 + k) mod m of the sorted sample, x its
+// key on the unit interval, target i_k / m.
+template <bool TRAIN>
+__global__ __launch_bounds__(256, 1) void cdf_grad_kernel(
+    const float *__restrict__ p, const float *__restrict__ x, const float *__restrict__ tgt,
+    const int32_t *__restrict__ sorted, int64_t m, uint64_t seed, uint64_t step, int64_t b,
+    float *__restrict__ partial)
+{
+    constexpr int LD = H + 1;
+    __shared__ float turn[4][2][H * LD];  // dz2 and h1, [sample][unit]
+    __shared__ float sums[4][NP + 1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int s = lane & 31, g = lane >> 5;
+    const float *W1 = p, *b1 = p + H, *W2 = p + 2 * H, *b2 = p + 2 * H + H * H;
+    const float *W3 = p + 3 * H + H * H;
+    const float b3 = p[4 * H + H * H];
+    float w1[16], c1[16], c2[16], w3[16], w2a[16], w2t[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int u = unit(r, g);
+        w1[r] = W1[u];
+        c1[r] = b1[u];
+        c2[r] = b2[u];
+        w3[r] = W3[u];
+        w2a[r] = W2[s * H + u];
+        w2t[r] = W2[u * H + s];
+    }
+    float gw1[16], gb1[16], gb2[16], gw3[16], gb3 = 0.0f, loss = 0.0f;
+    f32x16 gw2;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        gw1[r] = gb1[r] = gb2[r] = gw3[r] = gw2[r] = 0.0f;
+
+    for (int64_t i0 = (int64_t)blockIdx.x * CHUNK; i0 < b; i0 += (int64_t)gridDim.x * CHUNK) {
+        const int64_t i = i0 + wave * 32 + s;
+        const bool in = i < b;
+        float xi = 0.0f, ti = 0.0f;
+        if (in) {
+            if constexpr (TRAIN) {
+                const int64_t k =
+                    (int64_t)(splitmix64(seed, (step << 32) + (uint64_t)i) % (uint64_t)m);
+                xi = key_to_unit(sorted[k]);
+                ti = (float)((double)k / (double)m);
+            } else {
+                xi = x[i];
+                ti = tgt[i];
+            }
+        }
+        float h1[16];
+        f32x16 z2;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            h1[r] = fmaxf(fmaf(w1[r], xi, c1[r]), 0.0f);
+            z2[r] = c2[r];
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            z2 = __builtin_amdgcn_mfma_f32_32x32x2f32(w2a[r], h1[r], z2, 0, 0, 0);
+        float y = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            y = fmaf(w3[r], fmaxf(z2[r], 0.0f), y);
+        y += __shfl_xor(y, 32) + b3;
+        const float diff = in ? y - ti : 0.0f;
+        const float dy = in ? 2.0f * diff / (float)b : 0.0f;
+        gb3 += dy;
+        loss = fmaf(diff, diff, loss);
+        float dz2[16];
+        f32x16 dh;
+        float *tz = turn[wave][0], *th = turn[wave][1];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            dz2[r] = in && z2[r] > 0.0f ? dy * w3[r] : 0.0f;
+            gw3[r] = fmaf(dy, fmaxf(z2[r], 0.0f), gw3[r]);
+            gb2[r] += dz2[r];
+            dh[r] = 0.0f;
+            tz[s * LD + unit(r, g)] = dz2[r];
+            th[s * LD + unit(r, g)] = in ? h1[r] : 0.0f;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            dh = __builtin_amdgcn_mfma_f32_32x32x2f32(w2t[r], dz2[r], dh, 0, 0, 0);
+        // one wave's LDS operations complete in order; keep the compiler to it
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            gw2 = __builtin_amdgcn_mfma_f32_32x32x2f32(tz[(2 * r + g) * LD + s],
+                                                      th[(2 * r + g) * LD + s], gw2, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float dz1 = h1[r] > 0.0f ? dh[r] : 0.0f;
+            gw1[r] = fmaf(dz1, xi, gw1[r]);
+            gb1[r] += dz1;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int u = unit(r, g);
+        const float a1 = half_sum(gw1[r]), a2 = half_sum(gb1[r]);
+        const float a3 = half_sum(gb2[r]), a4 = half_sum(gw3[r]);
+        if (s == 31) {
+            sums[wave][u] = a1;
+            sums[wave][H + u] = a2;
+            sums[wave][2 * H + H * H + u] = a3;
+            sums[wave][3 * H + H * H + u] = a4;
+        }
+        sums[wave][2 * H + u * H + s] = gw2[r];
+    }
+    gb3 = half_sum(gb3);
+    loss = half_sum(loss);
+    if (lane == 31) {
+        sums[wave][NP - 1] = gb3;
+        sums[wave][NP] = loss;
+    }
     __syncthreads();
-    const float *W1 = P, *b1 = P + H, *W2 = P + 2 * H, *b2 = P + 2 * H + H * H;
-    const float *W3 = P + 3 * H + H * H;
-    const float b3 = P[4 * H + H * H];
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < b;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const float xi = x[i];
-        float h1[H], z2[H];
-#pragma unroll
-        for (int u = 0; u < H; ++u)
-            h1[u] = fmaf(W1[u], xi, b1[u]);  // z1 for now
-        float y = b3;
-#pragma unroll
-        for (int o = 0; o < H; ++o) {
-            float z = b2[o];
-#pragma unroll
-            for (int u = 0; u < H; ++u)
-                z = fmaf(W2[o * H + u], fmaxf(h1[u], 0.0f), z);
-            z2[o] = z;
-            y = fmaf(W3[o], fmaxf(z, 0.0f), y);
-        }
-        const float diff = y - tgt[i];
-        const float dy = 2.0f * diff / (float)b;
-        rec[0 * b + i] = xi;
-        rec[1 * b + i] = dy;
-        rec[2 * b + i] = diff * diff;
-        rec[3 * b + i] = 0.0f;
-        float dz2[H];
-#pragma unroll
-        for (int o = 0; o < H; ++o) {
-            dz2[o] = z2[o] > 0.0f ? dy * W3[o] : 0.0f;
-            rec[(4 + 2 * H + o) * b + i] = fmaxf(z2[o], 0.0f);  // h2
-            rec[(4 + 3 * H + o) * b + i] = dz2[o];
-        }
-#pragma unroll
-        for (int u = 0; u < H; ++u) {
-            float dh = 0.0f;
-#pragma unroll
-            for (int o = 0; o < H; ++o)
-                dh = fmaf(dz2[o], W2[o * H + u], dh);
-            rec[(4 + u) * b + i] = fmaxf(h1[u], 0.0f);                  // h1
-            rec[(4 + H + u) * b + i] = h1[u] > 0.0f ? dh : 0.0f;       // dz1
-        }
-    }
+    for (int j = threadIdx.x; j <= NP; j += 256)
+        partial[(int64_t)blockIdx.x * (NP + 1) + j] =
+            (sums[0][j] + sums[1][j]) + (sums[2][j] + sums[3][j]);
 }
 
-// Factor pair of gradient entry j: g_j = sum_i rec[fa(j)][i] * rec[fb(j)][i]
-// (fb = -1 means a plain sum); entry NP is the loss (sum of squares / b).
-__device__ __forceinline__ void entry_fields(int j, int &fa, int &fb)
+struct AdamArgs {
+    float *p, *m, *v;
+    float lr, beta1, beta2, eps, bc1, bc2;
+};
+
+__device__ __forceinline__ void adam_entry(const AdamArgs &a, int j, float gj)
 {
-    if (j < H) {                 // W1[u]: dz1[u] * x
-        fa = 4 + H + j;
-        fb = 0;
-    } else if (j < 2 * H) {      // b1[u]: dz1[u]
-        fa = 4 + H + (j - H);
-        fb = -1;
-    } else if (j < 2 * H + H * H) {  // W2[o][u]: dz2[o] * h1[u]
-        const int q = j - 2 * H;
-        fa = 4 + 3 * H + q / H;
-        fb = 4 + q % H;
-    } else if (j < 3 * H + H * H) {  // b2[o]: dz2[o]
-        fa = 4 + 3 * H + (j - 2 * H - H * H);
-        fb = -1;
-    } else if (j < 4 * H + H * H) {  // W3[o]: dy * h2[o]
-        fa = 1;
-        fb = 4 + 2 * H + (j - 3 * H - H * H);
-    } else if (j < NP) {         // b3: dy
-        fa = 1;
-        fb = -1;
-    } else {                     // loss: sq
-        fa = 2;
-        fb = -1;
-    }
+    const float mj = a.beta1 * a.m[j] + (1.0f - a.beta1) * gj;
+    const float vj = a.beta2 * a.v[j] + (1.0f - a.beta2) * gj * gj;
+    a.m[j] = mj;
+    a.v[j] = vj;
+    a.p[j] -= a.lr * (mj / a.bc1) / (sqrtf(vj / a.bc2) + a.eps);
 }
 
-// Phase 2: partial[c * (NP + 1) + j] = sum over the samples of chunk c.
-__global__ __launch_bounds__(256) void cdf_bwd_partial_kernel(const float *__restrict__ rec,
-                                                              float *__restrict__ partial, int64_t b)
+// Entry j's partials: 16 threads add every sixteenth row, then the sixteen
+// sums are added in order.  A workgroup takes 64 entries, so that the rows
+// are read in 256-byte pieces and all at once.  ADAM: the entry's Adam step
+// follows, and grad and loss are not stored.
+template <bool ADAM>
+__global__ __launch_bounds__(1024) void cdf_reduce_kernel(const float *__restrict__ partial,
+                                                          int rows, int64_t b,
+                                                          float *__restrict__ grad,
+                                                          float *__restrict__ loss, AdamArgs a)
 {
-    __shared__ float R[NREC][CHUNK];
-    const int64_t c = blockIdx.x;
-    const int64_t i0 = c * CHUNK;
-    const int cnt = (int)(b - i0 < CHUNK ? b - i0 : CHUNK);
-    for (int q = threadIdx.x; q < NREC * CHUNK; q += blockDim.x) {
-        const int f = q / CHUNK, k = q % CHUNK;
-        R[f][k] = k < cnt ? rec[f * b + i0 + k] : 0.0f;
-    }
-    __syncthreads();
-    for (int j = threadIdx.x; j <= NP; j += blockDim.x) {
-        int fa, fb;
-        entry_fields(j, fa, fb);
-        float s = 0.0f;
-        if (fb < 0) {
-            for (int k = 0; k < cnt; ++k)
-                s += R[fa][k];
-        } else {
-            for (int k = 0; k < cnt; ++k)
-                s = fmaf(R[fa][k], R[fb][k], s);
-        }
-        partial[c * (NP + 1) + j] = s;
-    }
-}
-
-// Phase 3: chunk partials in chunk order.
-__global__ __launch_bounds__(256) void cdf_bwd_final_kernel(const float *__restrict__ partial,
-                                                            int64_t nchunks, int64_t b,
-                                                            float *__restrict__ grad,
-                                                            float *__restrict__ loss)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j > NP)
-        return;
+    __shared__ float part[16][64];
+    const int e = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int j = blockIdx.x * 64 + e;
     float s = 0.0f;
-    for (int64_t c = 0; c < nchunks; ++c)
-        s += partial[c * (NP + 1) + j];
-    if (j < NP)
-        grad[j] = s;
-    else
-        loss[0] = s / (float)b;
+    if (j <= NP) {
+#pragma unroll 16
+        for (int c = q; c < rows; c += 16)
+            s += partial[(int64_t)c * (NP + 1) + j];
+    }
+    part[q][e] = s;
+    __syncthreads();
+    if (q != 0 || j > NP)
+        return;
+    s = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 16; ++c)
+        s += part[c][e];
+    if constexpr (ADAM) {
+        if (j < NP)
+            adam_entry(a, j, s);
+    } else {
+        if (j < NP)
+            grad[j] = s;
+        else
+            loss[0] = s / (float)b;
+    }
 }
 
-__global__ __launch_bounds__(256) void cdf_adam_kernel(float *__restrict__ p, float *__restrict__ m,
-                                                       float *__restrict__ v,
-                                                       const float *__restrict__ g, float lr,
-                                                       float beta1, float beta2, float eps,
-                                                       float bc1, float bc2)
+__global__ __launch_bounds__(256) void cdf_adam_kernel(const float *__restrict__ g, AdamArgs a)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= NP)
-        return;
-    const float gj = g[j];
-    const float mj = beta1 * m[j] + (1.0f - beta1) * gj;
-    const float vj = beta2 * v[j] + (1.0f - beta2) * gj * gj;
-    m[j] = mj;
-    v[j] = vj;
-    p[j] -= lr * (mj / bc1) / (sqrtf(vj / bc2) + eps);
+    if (j < NP)
+        adam_entry(a, j, g[j]);
 }
 
 __global__ void cdf_zero_kernel(float *__restrict__ a, float *__restrict__ b)
@@ -210,23 +285,6 @@ __global__ void cdf_zero_kernel(float *__restrict__ a, float *__restrict__ b)
         a[j] = 0.0f;
         b[j] = 0.0f;
     }
-}
-
-// Minibatch of training step `step`: position i_k = SplitMix64(seed, step *
-// 2^32 + k) mod m of the sorted sample; x_k its key on the unit interval,
-// target i_k / m.
-__global__ __launch_bounds__(256) void cdf_batch_kernel(const int32_t *__restrict__ sorted,
-                                                        int64_t m, int64_t batch, uint64_t seed,
-                                                        uint64_t step, float *__restrict__ x,
-                                                        float *__restrict__ t)
-{
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= batch)
-        return;
-    const uint64_t r = splitmix64(seed, (step << 32) + (uint64_t)k);
-    const int64_t i = (int64_t)(r % (uint64_t)m);
-    x[k] = key_to_unit(sorted[i]);
-    t[k] = (float)((double)i / (double)m);
 }
 
 // out[k] = keys[SplitMix64(seed, k) mod n]: a uniform sample with replacement.
@@ -239,62 +297,43 @@ __global__ __launch_bounds__(256) void cdf_sample_kernel(const int32_t *__restri
         out[k] = keys[splitmix64(seed, (uint64_t)k) % (uint64_t)n];
 }
 
+// The workspace is sized by NREC floats per sample and a row of partials per
+// CHUNK of them; the kernels use the rows of at most GRAD_WGS workgroups.
 struct BwdWs {
-    int64_t rec, partial, total;
+    int64_t partial, total;
 };
 
 BwdWs bwd_layout(int64_t b)
 {
     BwdWs w;
     const int64_t nchunks = (b + CHUNK - 1) / CHUNK;
-    w.rec = 0;
     w.partial = ((NREC * b * 4) + 255) & ~(int64_t)255;
     w.total = w.partial + (((nchunks * (NP + 1) * 4) + 255) & ~(int64_t)255);
     return w;
 }
 
-hipError_t backward(const float *p, const float *x, const float *t, float *grad, float *loss,
-                    int64_t b, char *ws, hipStream_t s)
+int grad_rows(int64_t b)
 {
-    const BwdWs w = bwd_layout(b);
-    float *rec = (float *)(ws + w.rec);
-    float *partial = (float *)(ws + w.partial);
-    const int64_t nchunks = (b + CHUNK - 1) / CHUNK;
-    int64_t blocks = (b + 255) / 256;
-    if (blocks > 4096)
-        blocks = 4096;
-    hipLaunchKernelGGL(cdf_bwd_samples_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p, x, t,
-                       rec, b);
-    hipLaunchKernelGGL(cdf_bwd_partial_kernel, dim3((unsigned)nchunks), dim3(256), 0, s, rec,
-                       partial, b);
-    hipLaunchKernelGGL(cdf_bwd_final_kernel, dim3((NP + 1 + 255) / 256), dim3(256), 0, s, partial,
-                       nchunks, b, grad, loss);
-    return hipGetLastError();
+    const int64_t chunks = (b + CHUNK - 1) / CHUNK;
+    return (int)(chunks < GRAD_WGS ? chunks : GRAD_WGS);
 }
 
-hipError_t adam(float *p, float *m, float *v, const float *g, int step, float lr, float beta1,
-                float beta2, float eps, hipStream_t s)
+AdamArgs adam_args(float *p, float *m, float *v, int step, float lr, float beta1, float beta2,
+                   float eps)
 {
-    const float bc1 = (float)(1.0 - pow((double)beta1, (double)step));
-    const float bc2 = (float)(1.0 - pow((double)beta2, (double)step));
-    hipLaunchKernelGGL(cdf_adam_kernel, dim3((NP + 255) / 256), dim3(256), 0, s, p, m, v, g, lr,
-                       beta1, beta2, eps, bc1, bc2);
-    return hipGetLastError();
+    return {p, m, v, lr, beta1, beta2, eps, (float)(1.0 - pow((double)beta1, (double)step)),
+            (float)(1.0 - pow((double)beta2, (double)step))};
 }
 
 struct TrainWs {
-    int64_t x, t, grad, loss, bwd, total;
+    int64_t bwd, total;
 };
 
 TrainWs train_layout(int64_t batch)
 {
     TrainWs w;
     auto a = [](int64_t v) { return (v + 255) & ~(int64_t)255; };
-    w.x = 0;
-    w.t = a(batch * 4);
-    w.grad = w.t + a(batch * 4);
-    w.loss = w.grad + a(NP * 4);
-    w.bwd = w.loss + 256;
+    w.bwd = 2 * a(batch * 4) + a(NP * 4) + 256;  // bytes before it: unused
     w.total = w.bwd + bwd_layout(batch).total;
     return w;
 }
@@ -360,8 +399,14 @@ int hvms_cdf_backward(const float *d_params, const float *d_x, const float *d_t,
     const int st = check(d_ws, ws_bytes, bwd_layout(b).total);
     if (st)
         return st;
-    return status(backward(d_params, d_x, d_t, d_grad, d_loss, b, (char *)d_ws,
-                           (hipStream_t)stream));
+    float *partial = (float *)((char *)d_ws + bwd_layout(b).partial);
+    const int rows = grad_rows(b);
+    hipLaunchKernelGGL(cdf_grad_kernel<false>, dim3(rows), dim3(256), 0, (hipStream_t)stream,
+                       d_params, d_x, d_t, nullptr, (int64_t)0, (uint64_t)0, (uint64_t)0, b,
+                       partial);
+    hipLaunchKernelGGL(cdf_reduce_kernel<false>, dim3((NP + 64) / 64), dim3(1024), 0,
+                       (hipStream_t)stream, partial, rows, b, d_grad, d_loss, AdamArgs{});
+    return status(hipGetLastError());
 }
 
 int hvms_cdf_adam_step(float *d_params, float *d_m, float *d_v, const float *d_grad, int32_t step,
@@ -370,8 +415,10 @@ int hvms_cdf_adam_step(float *d_params, float *d_m, float *d_v, const float *d_g
     if (!d_params || !d_m || !d_v || !d_grad || step < 1 || !(beta1 >= 0.0f && beta1 < 1.0f) ||
         !(beta2 >= 0.0f && beta2 < 1.0f))
         return HVMS_ERR_INVALID_ARG;
-    return status(adam(d_params, d_m, d_v, d_grad, step, lr, beta1, beta2, eps,
-                       (hipStream_t)stream));
+    hipLaunchKernelGGL(cdf_adam_kernel, dim3((NP + 255) / 256), dim3(256), 0,
+                       (hipStream_t)stream, d_grad,
+                       adam_args(d_params, d_m, d_v, step, lr, beta1, beta2, eps));
+    return status(hipGetLastError());
 }
 
 int64_t hvms_cdf_train_workspace_bytes(int64_t batch)
@@ -393,16 +440,16 @@ int hvms_cdf_train(float *d_params, float *d_m, float *d_v, const int32_t *d_sor
         return st;
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)d_ws;
-    float *x = (float *)(ws + w.x), *t = (float *)(ws + w.t), *g = (float *)(ws + w.grad);
-    float *loss = (float *)(ws + w.loss);
+    float *partial = (float *)(ws + w.bwd + bwd_layout(batch).partial);
+    const int rows = grad_rows(batch);
     hipLaunchKernelGGL(cdf_zero_kernel, dim3((NP + 255) / 256), dim3(256), 0, s, d_m, d_v);
     for (int step = 1; step <= steps; ++step) {
-        hipLaunchKernelGGL(cdf_batch_kernel, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0,
-                           s, d_sorted, m, batch, seed, (uint64_t)(step - 1), x, t);
-        hipError_t e = backward(d_params, x, t, g, loss, batch, ws + w.bwd, s);
-        if (e == hipSuccess)
-            e = adam(d_params, d_m, d_v, g, step, lr, 0.9f, 0.999f, 1e-8f, s);
-        st = status(e);
+        hipLaunchKernelGGL(cdf_grad_kernel<true>, dim3(rows), dim3(256), 0, s, d_params, nullptr,
+                           nullptr, d_sorted, m, seed, (uint64_t)(step - 1), batch, partial);
+        hipLaunchKernelGGL(cdf_reduce_kernel<true>, dim3((NP + 64) / 64), dim3(1024), 0, s,
+                           partial, rows, batch, nullptr, nullptr,
+                           adam_args(d_params, d_m, d_v, step, lr, 0.9f, 0.999f, 1e-8f));
+        st = status(hipGetLastError());
         if (st)
             return st;
     }
