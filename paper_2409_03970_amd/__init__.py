@@ -191,11 +191,14 @@ def _on(stream):
 
 def _alloc_on_stream(fn):
     """Runs an allocating convenience inside _on(its `stream` argument)."""
-    sig = inspect.signature(fn)
+    at = list(inspect.signature(fn).parameters).index("stream")
 
     @functools.wraps(fn)
     def wrapper(*args, **kwargs):
-        with _on(sig.bind_partial(*args, **kwargs).arguments.get("stream")):
+        stream = args[at] if len(args) > at else kwargs.get("stream")
+        if stream is None:
+            return fn(*args, **kwargs)
+        with _on(stream):
             return fn(*args, **kwargs)
     return wrapper
 
