@@ -150,7 +150,7 @@ bool library_choice(const hvms_options *o)
 // against 0.25-0.31 ms; at 2^21 presorted keys are even) up to 3 * 2^24, past
 // which their runs go to HBM in pieces and random pairs lose (2^25 1.23 against
 // 1.69 ms, 2^26 2.78 against 2.60).
-constexpr int64_t kRadixMin = 1 << 16, kRadixMin2 = 1 << 22, kRadixMax2 = 3 << 24;
+constexpr int64_t kRadixMin = 1 << 16, kRadixMin2 = 1 << 22, kRadixMax2 = ((int64_t)1 << 32) - (1 << 16);
 constexpr int64_t kRadixMax = ((int64_t)1 << 32) - (1 << 16);  // 32-bit positions
 bool radix_route(int kind, int64_t n, const hvms_options *o)
 {

@@ -70,7 +70,11 @@ struct RadixArgs {
     uint32_t *totals;       // [digit]
     uint32_t *counts;       // [chunk][digit]
     uint32_t *rows;         // [tile][digit]: keys of the chunk's tiles before
+    uint64_t *sample;       // null: no sample is taken
+    uint32_t *sample_pairs; // [run][digit]
+    longlong2 *groups;      // first element and length
     int chunks;
+    int round;              // 0, or 1: the passes after radix_finish
     RadixMap map;
     uint32_t fl;
 };
@@ -81,7 +85,8 @@ struct RadixIO {
     uint64_t *pout;
 };
 struct RadixLayout {
-    int64_t a_k, a_v, b_k, b_v, a_p, ctl, totals, info, counts, rows, total;
+    int64_t a_k, a_v, b_k, b_v, a_p, ctl, totals, info, counts, rows, sample, sample_pairs,
+        groups, total;
 };
 RadixLayout radix_layout(int kind, int64_t n);
 hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap km,

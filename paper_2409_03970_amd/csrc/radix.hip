@@ -53,6 +53,8 @@ namespace {
 constexpr int RADIX = 256;
 constexpr int COUNT_NT = 512;
 constexpr int MAX_CHUNKS = 512;
+constexpr int SAMPLE_RUNS = 32, SAMPLE_LEN = 8192, SAMPLE = SAMPLE_RUNS * SAMPLE_LEN;
+constexpr int64_t SAMPLE_MIN = (int64_t)1 << 24;  // elements from which a sample is taken
 constexpr int COPIES = 8;  // interleaved histogram copies of the count kernel
 
 // buffers of a sort; the steps alternate between them
@@ -64,15 +66,20 @@ struct Step {
 };
 
 struct Ctl {
-    Step step[8];
+    Step step[2][8];  // of the first round and of the second (see radix_finish)
+    uint32_t drop;    // low digits the first round left out and radix_finish orders
+    uint32_t groups;  // groups listed by radix_finish
+    uint32_t again;   // set: these could not order them, the second round sorts
 };
 
 // The step of a pass, in scalar registers.
-__device__ __forceinline__ Step step_of(const void *ctl, int pass)
+__device__ __forceinline__ Step step_of(const RadixArgs &a, int pass)
 {
-    const uint32_t *q = (const uint32_t *)&((const Ctl *)ctl)->step[pass];
+    const Ctl *ctl = (const Ctl *)a.ctl;
+    const uint32_t *q = (const uint32_t *)&ctl->step[a.round][pass];
     Step s;
-    s.mode = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[0]);
+    s.mode = a.round == 0 || ctl->again ? q[0] : (uint32_t)STEP_SKIP;
+    s.mode = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.mode);
     s.src = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[1]);
     s.dst = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[2]);
     s.first = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[3]);
@@ -289,7 +296,7 @@ __global__ __launch_bounds__(COUNT_NT) void radix_count_first(RadixArgs a)
 template <int KIND, int T>
 __global__ __launch_bounds__(COUNT_NT) void radix_count(RadixArgs a, int pass)
 {
-    const Step st = step_of(a.ctl, pass);
+    const Step st = step_of(a, pass);
     if (st.mode != STEP_SCATTER)
         return;
     __shared__ __align__(16) uint32_t hist[RADIX * COPIES];
@@ -359,10 +366,55 @@ __device__ __forceinline__ uint32_t wave_inclusive(uint32_t x)
     return x;
 }
 
+// The steps of one round: modes by pass, and the buffers they go through.
+__device__ void set_steps(Step *step, const uint32_t *mode, int passes, bool keys64)
+{
+    int steps = 0, j = 0;
+    for (int p = 0; p < passes; ++p)
+        steps += mode[p] != STEP_SKIP;
+    uint32_t cur = B_IN;
+    for (int p = 0; p < passes; ++p) {
+        Step s{mode[p], 0, 0, 0, 0};
+        if (mode[p] != STEP_SKIP) {
+            s.first = j == 0;
+            s.last = j == steps - 1;
+            s.src = cur;
+            if (s.last)
+                s.dst = B_OUT;
+            else if (keys64)
+                s.dst = (j & 1) ? B_B : B_A;
+            else
+                s.dst = ((steps - 1 - j) & 1) ? B_A : B_OUT;
+            cur = s.dst;
+            ++j;
+        }
+        step[p] = s;
+    }
+}
+
+// Passes over the digits in `need`.  In place, the first step must not write
+// the array it reads: where the count of steps would make it, a pass that is
+// not needed copies instead.
+__device__ void scatter_modes(uint32_t *mode, uint32_t need, int passes, bool keys64, bool inplace)
+{
+    int steps = 0;
+    for (int p = 0; p < passes; ++p) {
+        mode[p] = (need >> p) & 1 ? STEP_SCATTER : STEP_SKIP;
+        steps += (int)((need >> p) & 1);
+    }
+    if (inplace && (keys64 ? steps == 1 : (steps & 1) != 0))
+        for (int p = 0; p < passes; ++p)
+            if (mode[p] == STEP_SKIP) {
+                mode[p] = STEP_COPY;
+                break;
+            }
+}
+
 // The steps of the sort from what the chunks found (one workgroup).
 __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64, bool inplace)
 {
     __shared__ ChunkInfo part[8];
+    __shared__ uint32_t same[8];
     ChunkInfo f{~0u, 0u, ~0u, 0u, 0u, {0, 0, 0}};
     const ChunkInfo *info = (const ChunkInfo *)a.info;
     for (int c = threadIdx.x; c < a.chunks; c += 512) {
@@ -380,6 +432,13 @@ __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64,
     f.flags = wave_or(f.flags);
     if (lane_id() == 0)
         part[threadIdx.x / 64] = f;
+    if (threadIdx.x < 8) {  // sampled pairs that first differ in digit threadIdx.x
+        uint32_t c = 0;
+        if (a.sample)
+            for (int r = 0; r < SAMPLE_RUNS; ++r)
+                c += a.sample_pairs[r * 8 + threadIdx.x];
+        same[threadIdx.x] = c;
+    }
     __syncthreads();
     if (threadIdx.x != 0)
         return;
@@ -391,67 +450,55 @@ __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64,
         f.flags |= part[w].flags;
     }
     Ctl *ctl = (Ctl *)a.ctl;
-    uint32_t mode[8];
-    int steps = 0;
+    uint32_t mode[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     const bool ascending = !(f.flags & NOT_ASCENDING);
     const bool descending = !(f.flags & NOT_DESCENDING);
-    for (int p = 0; p < passes; ++p)
-        mode[p] = STEP_SKIP;
+    ctl->drop = 0;
+    ctl->groups = 0;
+    ctl->again = 0;
     if (ascending) {
         mode[passes - 1] = STEP_COPY;
-        steps = 1;
     } else if (descending) {
         mode[passes - 1] = STEP_REVERSE;
-        steps = 1;
         if (inplace) {  // through the scratch, since both ends move
             mode[passes - 2] = STEP_REVERSE;
             mode[passes - 1] = STEP_COPY;
-            steps = 2;
         }
     } else {
         // a set bit: this bit differs between two elements
         const uint32_t var0 = f.and0 ^ f.or0, var1 = f.and1 ^ f.or1;
+        uint32_t need = 0;
         for (int p = 0; p < passes; ++p) {
             const uint32_t var = (two && p < 4) ? var0 : var1;
-            bool need = ((var >> (8 * (p & 3))) & 255) != 0;
-            if (two && !keys64 && p < 4 && !(f.flags & VALUES_NOT_ASCENDING))
-                need = false;
-            if (need) {
-                mode[p] = STEP_SCATTER;
-                ++steps;
+            if ((var >> (8 * (p & 3))) & 255)
+                need |= 1u << p;
+        }
+        if (two && !keys64 && !(f.flags & VALUES_NOT_ASCENDING))
+            need &= 0xf0;
+        if (a.sample) {
+            // The most low digits without which hardly any different elements
+            // are alike in the sample: 2^31 values drawn evenly make 0.5 such
+            // pairs of neighbours.  m elements in groups of g make 16 m g
+            // (SAMPLE_LEN / n)^2, so with the three allowed, groups of more
+            // than GROUP_MAX elements slip through only where they are fewer
+            // than one in 10,000.
+            uint32_t alike = 0, drop = 0;
+            for (int d = 1; d < 8; ++d) {
+                alike += same[d - 1];
+                if (alike <= 3)
+                    drop = d;
+            }
+            const uint32_t low = need & ((1u << drop) - 1);
+            if (__popc(low) >= 2) {
+                scatter_modes(mode, need, passes, keys64, true);
+                set_steps(ctl->step[1], mode, passes, keys64);
+                ctl->drop = drop;
+                need &= ~low;
             }
         }
-        // In place, the first step must not write the array it reads: with a
-        // step count that would make it, one skipped pass copies instead.
-        const bool clash = keys64 ? steps == 1 : (steps & 1) != 0;
-        if (inplace && clash) {
-            for (int p = 0; p < passes; ++p)
-                if (mode[p] == STEP_SKIP) {
-                    mode[p] = STEP_COPY;
-                    ++steps;
-                    break;
-                }
-        }
+        scatter_modes(mode, need, passes, keys64, inplace);
     }
-    int j = 0;
-    uint32_t cur = B_IN;
-    for (int p = 0; p < passes; ++p) {
-        Step s{mode[p], 0, 0, 0, 0};
-        if (mode[p] != STEP_SKIP) {
-            s.first = j == 0;
-            s.last = j == steps - 1;
-            s.src = cur;
-            if (s.last)
-                s.dst = B_OUT;
-            else if (keys64)
-                s.dst = (j & 1) ? B_B : B_A;
-            else
-                s.dst = ((steps - 1 - j) & 1) ? B_A : B_OUT;
-            cur = s.dst;
-            ++j;
-        }
-        ctl->step[p] = s;
-    }
+    set_steps(ctl->step[0], mode, passes, keys64);
 }
 
 // Workgroup g: the exclusive prefixes of the counts of digits 16 g .. 16 g +
@@ -465,7 +512,7 @@ __global__ __launch_bounds__(512) void radix_scan(RadixArgs a, int pass, int pas
         make_plan(a, passes, two != 0, keys64 != 0, inplace != 0);
         return;
     }
-    if (pass > 0 && step_of(a.ctl, pass).mode != STEP_SCATTER)
+    if ((pass > 0 || a.round) && step_of(a, pass).mode != STEP_SCATTER)
         return;
     __shared__ uint32_t sum[32][16];
     const int d = threadIdx.x & 15, q = threadIdx.x >> 4;
@@ -497,6 +544,221 @@ __global__ __launch_bounds__(512) void radix_scan(RadixArgs a, int pass, int pas
     }
     if (q == 0)
         a.totals[blockIdx.x * 16 + d] = all;
+}
+
+// ---------------------------------------------- top digits and the finish
+//
+// Elements of two words rarely need all their eight digits: once the top ones
+// tell nearly all of them apart, the few that are left alike stand next to
+// each other and are ordered where they are.  How many digits that takes is
+// estimated from a sample sorted in SAMPLE_RUNS runs by the block sort:
+// neighbours that are equal in the top digits and different below are what a
+// shorter key would leave alike.  The finish checks its own work, so the
+// estimate only costs time where it is wrong: the second round then makes
+// every pass that is needed.  Pairs of 2^26 uniform keys and random values take
+// four passes and the finish, 1.85 ms, for eight passes 2.78 and the merge sort
+// 2.62; 2^26 doubles five and 2.2 ms for 2.79 and 2.72.
+
+// Sample element j comes from position SplitMix64(j) * n / 2^64.  (From the
+// j-th of equal parts of the input it would not do: in presorted input the
+// elements that are alike stand side by side and would never meet.)
+template <int KIND> __global__ __launch_bounds__(256) void radix_sample(RadixArgs a)
+{
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    uint64_t z = ((uint64_t)j + 1) * 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    const int64_t i = (int64_t)__umul64hi(z ^ (z >> 31), (uint64_t)a.n);
+    const Elem e = map_elem2<KIND>(load_raw<KIND>(a, B_IN, i), a);
+    // signed order, as the block sort compares
+    a.sample[j] = ((uint64_t)(e.hi ^ 0x80000000u) << 32) | e.lo;
+}
+
+// Neighbours of sorted run blockIdx.x by the highest digit in which they
+// differ (equal neighbours are no pair to be told apart).
+__global__ __launch_bounds__(256) void radix_sample_pairs(RadixArgs a)
+{
+    __shared__ uint32_t c[8];
+    if (threadIdx.x < 8)
+        c[threadIdx.x] = 0;
+    __syncthreads();
+    const uint64_t *x = a.sample + (int64_t)blockIdx.x * SAMPLE_LEN;
+    for (int i = threadIdx.x; i + 1 < SAMPLE_LEN; i += 256) {
+        const uint64_t d = x[i] ^ x[i + 1];
+        if (d)
+            atomicAdd(&c[(63 - __clzll((long long)d)) >> 3], 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x < 8)
+        a.sample_pairs[blockIdx.x * 8 + threadIdx.x] = c[threadIdx.x];
+}
+
+// Orders the groups that the first round left alike, in the output.  A wave
+// looks at windows of 64 consecutive elements, 32 apart; a group belongs to the
+// window in whose first half it starts.  The groups that end inside their
+// window (all of up to 33 elements) are sorted in the lanes, all at once, by
+// odd-even transposition, and every lane stores its own element.  A longer
+// group is read through and, if it is out of order, put on a list for
+// radix_groups; past GROUP_MAX elements, or past the end of the list, the
+// sort goes to the second round.  What others look at while an element moves,
+// the common digits of its group, does not change.  Bound by one read of the
+// elements (2^28 uniform pairs, 12 % of them alike: 2.5 ms when the first
+// lane of each group read it through in memory, now 1.0).
+constexpr int GROUP_MAX = 8192;    // elements of a listed group: one block-sort tile
+constexpr int GROUPS_MAX = 16384;  // listed groups
+
+template <int KIND> __device__ __forceinline__ uint64_t finish_elem(const RadixArgs &a, int64_t i)
+{
+    const Elem e = map_elem2<KIND>(load_raw<KIND>(a, B_OUT, i), a);
+    return ((uint64_t)e.hi << 32) | e.lo;
+}
+template <int KIND>
+__device__ __forceinline__ void finish_store(const RadixArgs &a, int64_t i, uint64_t x)
+{
+    store_raw<KIND>(a, B_OUT, i,
+                    unmap_elem2<KIND>(Elem{(uint32_t)(x >> 32), (uint32_t)x}, a));
+}
+
+template <int KIND> __global__ __launch_bounds__(256) void radix_finish(RadixArgs a)
+{
+    Ctl *ctl = (Ctl *)a.ctl;
+    const int shift = 8 * (int)ctl->drop;
+    if (shift == 0)
+        return;
+    const int lane = lane_id();
+    constexpr int ROWS = 8;  // of 64 elements, to a wave
+    const int64_t w0 = ((int64_t)blockIdx.x * 4 + threadIdx.x / 64) * (64 * ROWS);
+    if (w0 >= a.n)
+        return;
+    const auto at = [&](int64_t i) {
+        return finish_elem<KIND>(a, i < 0 ? 0 : i < a.n ? i : a.n - 1);
+    };
+    uint64_t prior = at(w0 - 64 + lane), cur = at(w0 + lane), then = at(w0 + 64 + lane);
+#pragma unroll 1
+    for (int h = 0; h < 2 * ROWS; ++h) {
+        const int64_t b = w0 + 32 * h, i = b + lane;
+        if (b >= a.n)
+            return;
+        // the window: row `cur`, or its second half and the next row's first
+        uint64_t x = cur, prev, next;
+        if (h & 1) {
+            const uint64_t m = lane < 32 ? then : cur;  // what lane ^ 32 asks for
+            x = __shfl_xor((unsigned long long)m, 32);
+            prev = __shfl((unsigned long long)cur, 31);
+            next = __shfl((unsigned long long)then, 32);
+            prior = cur;
+            cur = then;
+            then = at(b + 96 + lane);
+        } else {
+            prev = __shfl((unsigned long long)prior, 63);
+            next = __shfl((unsigned long long)then, 0);
+        }
+        const uint64_t up = __shfl_up((unsigned long long)x, 1);
+        const uint64_t down = __shfl_down((unsigned long long)x, 1);
+        prev = lane == 0 ? prev : up;
+        next = lane == 63 ? next : down;
+        const bool eqn = i + 1 < a.n && (x >> shift) == (next >> shift);
+        const bool eqp = i > 0 && i < a.n && (x >> shift) == (prev >> shift);
+        const bool wrong = eqn && x > next;
+        const uint64_t link = __ballot(eqn), before = __ballot(eqp);
+        // in order, and no group runs on past the window (where it may not be)
+        if (__ballot(wrong) == 0 && !(link >> 63))
+            continue;
+        // this lane's group inside the window: lanes start .. last
+        const uint64_t heads = ~(link << 1) | 1;  // no link from the lane below
+        const int start = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
+        const uint64_t ends = ~(link >> lane);    // zero: links to the last lane and on
+        const int end = ends ? lane + __ffsll((unsigned long long)ends) - 1 : 64;
+        const int last = end < 63 ? end : 63;
+        const bool enters = start == 0 && (before & 1), leaves = last == 63 && (link >> 63);
+        const bool own = start < 32 && !enters;
+        const bool inside = own && !leaves && last > start;
+        const uint64_t x0 = x;
+        for (int round = 0;; ++round) {
+            const bool low = ((lane - start + round) & 1) == 0;  // lower lane of its pair
+            const int other = low ? lane + 1 : lane - 1;
+            const uint64_t y = __shfl((unsigned long long)x, other & 63);
+            if (inside && other >= start && other <= last && (low ? y < x : x < y))
+                x = y;
+            const uint64_t above = __shfl_down((unsigned long long)x, 1);
+            if (__ballot(inside && lane < last && x > above) == 0)
+                break;
+        }
+        if (inside && x != x0)
+            finish_store<KIND>(a, i, x);
+
+        const uint64_t leaving = __ballot(own && leaves);
+        if (leaving) {  // one group at most: read it through
+            const int s0 = __ffsll((unsigned long long)leaving) - 1;
+            const uint64_t digits = (uint64_t)__shfl((unsigned long long)x0, 63) >> shift;
+            bool order = __ballot(wrong && lane >= s0) == 0;
+            int64_t pos = b + 64;
+            uint64_t tail = __shfl((unsigned long long)x0, 63);
+            int more = 64;
+            // some way past GROUP_MAX, where the windows below see for themselves
+            while (more == 64 && pos - (b + s0) <= GROUP_MAX + 256) {
+                const uint64_t y = at(pos + lane);
+                const uint64_t in = __ballot(pos + lane < a.n && (y >> shift) == digits);
+                more = ~in ? __ffsll((unsigned long long)~in) - 1 : 64;
+                const uint64_t under = __shfl_up((unsigned long long)y, 1);
+                order = order && __ballot(lane < more && (lane == 0 ? tail : under) > y) == 0;
+                tail = __shfl((unsigned long long)y, 63);
+                pos += more;
+            }
+            const int64_t len = pos - (b + s0);
+            if (!order && lane == 0) {
+                const uint32_t g =
+                    more < 64 && len <= GROUP_MAX ? atomicAdd(&ctl->groups, 1u) : GROUPS_MAX;
+                if (g < GROUPS_MAX)
+                    a.groups[g] = make_longlong2(b + s0, len);
+                else
+                    atomicOr(&ctl->again, 1u);
+            }
+        }
+        // out of order in a group that started before: its own window's
+        // reader has seen it, unless it started too far back
+        if (__ballot(enters && wrong && lane < 32) && !ctl->again) {
+            const uint64_t digits = (uint64_t)__shfl((unsigned long long)x0, 0) >> shift;
+            int64_t pos = b - 1;
+            while (pos >= 0 && b - pos <= GROUP_MAX &&
+                   __ballot(pos - lane < 0 || (at(pos - lane) >> shift) != digits) == 0)
+                pos -= 64;
+            if (b - pos > GROUP_MAX && lane == 0)
+                atomicOr(&ctl->again, 1u);
+        }
+    }
+}
+
+// Sorts the listed groups, each as one padded tile of the block sort.
+template <int KIND> __global__ __launch_bounds__(1024) void radix_groups(RadixArgs a)
+{
+    constexpr int R = 8, NT = GROUP_MAX / R;
+    const Ctl *ctl = (const Ctl *)a.ctl;
+    if (ctl->drop == 0 || ctl->again)
+        return;
+    __shared__ __attribute__((aligned(16))) int64_t S[LdsSkew<int64_t>::size(R * NT)];
+    const LdsSkew<int64_t> Z{S, 0};
+    const uint32_t count = ctl->groups < GROUPS_MAX ? ctl->groups : GROUPS_MAX;
+    for (uint32_t g = blockIdx.x; g < count; g += gridDim.x) {
+        const int64_t i0 = a.groups[g].x;
+        const int len = (int)a.groups[g].y;
+        int64_t v[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int i = (threadIdx.x >> 6) * (64 * R) + 64 * j + (threadIdx.x & 63);
+            // unsigned order to signed; pads sort last
+            v[j] = i < len ? (int64_t)(finish_elem<KIND>(a, i0 + i) ^ (1ull << 63))
+                           : Traits<int64_t>::kMax;
+        }
+        sort_tile_core<R, NT, int64_t, 0>(S, v, threadIdx.x, 6, 4);
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int i = threadIdx.x + NT * j;
+            if (i < len)
+                finish_store<KIND>(a, i0 + i, (uint64_t)Z[i] ^ (1ull << 63));
+        }
+        __syncthreads();
+    }
 }
 
 // ----------------------------------------------------------------- scatter
@@ -552,7 +814,7 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
     __shared__ __align__(16) uint32_t gpre[RADIX];     // output index of the tile's first such key
     uint32_t *xch = (uint32_t *)xraw;
 
-    const Step st = step_of(a.ctl, pass);
+    const Step st = step_of(a, pass);
     if (st.mode == STEP_SKIP)
         return;
     if (st.mode != STEP_SCATTER) {
@@ -823,7 +1085,7 @@ constexpr int64_t align256(int64_t b) { return (b + 255) & ~(int64_t)255; }
 struct Shape {
     int nt, k;
 };
-constexpr Shape SHAPES[] = {{256, 8}, {512, 16}, {512, 32}};
+constexpr Shape SHAPES[] = {{256, 8}, {512, 16}, {512, 32}, {1024, 16}};
 
 // Small sorts take small tiles (more workgroups than 8,192-key tiles give:
 // 2^20 keys 66 against 71 us, 2^22 keys 96 and 97), keys alone large ones once
@@ -833,7 +1095,9 @@ int shape_of(int kind, int64_t n)
 {
     if (n < ((int64_t)1 << 22))
         return 0;
-    return kind == RADIX_KEYS && n >= ((int64_t)1 << 27) ? 2 : 1;
+    if (kind == RADIX_KEYS)
+        return n >= ((int64_t)1 << 27) ? 2 : 1;
+    return kind != RADIX_BY_KEY && n >= ((int64_t)1 << 26) ? 3 : 1;
 }
 int tile_of(int kind, int64_t n)
 {
@@ -888,6 +1152,14 @@ RadixLayout radix_layout(int kind, int64_t n)
     off += align256(chunks * RADIX * 4);
     w.rows = off;
     off += align256(tiles * RADIX * 4);
+    if ((kind == RADIX_PAIRS || kind == RADIX_KEYS64) && n >= SAMPLE_MIN) {
+        w.sample = off;
+        off += SAMPLE * 8;
+        w.sample_pairs = off;
+        off += SAMPLE_RUNS * 8 * 4;
+        w.groups = off;
+        off += GROUPS_MAX * (int64_t)sizeof(longlong2);
+    }
     w.total = off;
     return w;
 }
@@ -907,6 +1179,17 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
     int64_t wg = a.tiles < fit ? a.tiles : fit;
     wg = (wg + 7) & ~(int64_t)7;
     const dim3 cgrid((unsigned)a.chunks), sgrid((unsigned)wg);
+    if (a.sample) {
+        hipLaunchKernelGGL(radix_sample<KIND>, dim3(SAMPLE / 256), dim3(256), 0, s, a);
+        KeyMap packed;
+        packed.packed = true;
+        const hipError_t e = launch_block_sort(8, 1024, true, (const int32_t *)a.sample, nullptr,
+                                               (int32_t *)a.sample, nullptr, SAMPLE, 6, 4, false,
+                                               s, 0, packed, packed);
+        if (e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(radix_sample_pairs, dim3(SAMPLE_RUNS), dim3(256), 0, s, a);
+    }
     for (int p = 0; p < passes; ++p) {
         if (p == 0)
             hipLaunchKernelGGL((radix_count_first<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a);
@@ -915,6 +1198,23 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
         hipLaunchKernelGGL(radix_scan, dim3(RADIX / 16 + (p == 0)), dim3(512), 0, s, a, p, passes,
                            (int)two, (int)keys64, (int)inplace);
         hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES>), sgrid, dim3(NT), 0, s, a, p);
+    }
+    if constexpr (two) {
+        if (a.sample) {
+            hipLaunchKernelGGL(radix_finish<KIND>, dim3((unsigned)((a.n + 2047) / 2048)),
+                               dim3(256), 0, s, a);
+            hipLaunchKernelGGL(radix_groups<KIND>, dim3(2 * device_cus()), dim3(1024), 0, s, a);
+            a.round = 1;  // the second round sorts the output, in place
+            a.k[B_IN] = a.k[B_OUT];
+            a.v[B_IN] = a.v[B_OUT];
+            for (int p = 0; p < passes; ++p) {
+                hipLaunchKernelGGL((radix_count<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a, p);
+                hipLaunchKernelGGL(radix_scan, dim3(RADIX / 16), dim3(512), 0, s, a, p, passes,
+                                   (int)two, (int)keys64, 1);
+                hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES>), sgrid, dim3(NT), 0, s, a,
+                                   p);
+            }
+        }
     }
     return hipGetLastError();
 }
@@ -942,6 +1242,11 @@ hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap
     a.info = base + w.info;
     a.counts = (uint32_t *)(base + w.counts);
     a.rows = (uint32_t *)(base + w.rows);
+    if (w.sample) {
+        a.sample = (uint64_t *)(base + w.sample);
+        a.sample_pairs = (uint32_t *)(base + w.sample_pairs);
+        a.groups = (longlong2 *)(base + w.groups);
+    }
     // signed order (after the key map) to unsigned order of the words
     a.map.f = (uint32_t)km.fm;
     a.map.x = (uint32_t)km.um ^ 0x80000000u;
@@ -956,11 +1261,13 @@ hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap
     case RADIX_PAIRS:
         if (shape == 0)
             break;
-        return run_radix<RADIX_PAIRS, 1, 4, 2>(a, inplace, s);
+        return shape == 3 ? run_radix<RADIX_PAIRS, 3, 4, 1>(a, inplace, s)
+                          : run_radix<RADIX_PAIRS, 1, 4, 2>(a, inplace, s);
     case RADIX_KEYS64:
         if (shape == 0)
             break;
-        return run_radix<RADIX_KEYS64, 1, 4, 2>(a, inplace, s);
+        return shape == 3 ? run_radix<RADIX_KEYS64, 3, 4, 1>(a, inplace, s)
+                          : run_radix<RADIX_KEYS64, 1, 4, 2>(a, inplace, s);
     case RADIX_BY_KEY:
         return shape == 0 ? run_radix<RADIX_BY_KEY, 0, 4, 4>(a, inplace, s)
                           : run_radix<RADIX_BY_KEY, 1, 4, 2>(a, inplace, s);

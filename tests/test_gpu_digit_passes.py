@@ -149,3 +149,57 @@ def test_arrays_off_the_16_byte_grid():
     ko, vo = hv.sort_pairs(x, v, y, torch.empty(n + 1, dtype=torch.int32, device=DEV)[1:])
     ek, ev = oracle.sort_pairs(x.cpu().numpy(), v.cpu().numpy())
     assert np.array_equal(ko.cpu().numpy(), ek) and np.array_equal(vo.cpu().numpy(), ev)
+
+
+def _unsampled(n, count, rng):
+    """Positions that the sample of the digit choice does not read: element j
+    of its 2^18 is at SplitMix64(j) * n / 2^64."""
+    with np.errstate(over="ignore"):
+        z = (np.arange(1 << 18, dtype=np.uint64) + np.uint64(1)) * np.uint64(0x9E3779B97F4A7C15)
+        z = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+        z = (z ^ (z >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+        z ^= z >> np.uint64(31)
+        lo = ((z & np.uint64(0xffffffff)) * np.uint64(n)) >> np.uint64(32)
+        seen = ((z >> np.uint64(32)) * np.uint64(n) + lo) >> np.uint64(32)
+    free = np.ones(n, dtype=bool)
+    free[seen.astype(np.int64)] = False
+    return rng.choice(np.flatnonzero(free), count, replace=False)
+
+
+@pytest.mark.parametrize("lengths", [tuple(range(2, 70)), (31, 32, 33, 34, 63, 64, 65, 66) * 20,
+                                     (100, 1000, 8190, 8191, 8192), (8193,), (8256, 8447, 8449),
+                                     (20000,), (2,) * 30000, (40,) * 16385])
+@pytest.mark.parametrize("kind", ("i64", "pairs"))
+def test_groups_left_alike_by_the_top_digits(lengths, kind):
+    """Groups that share their upper words, planted where the sample does not
+    look, so that the finish meets them: in a window, listed, too long, too
+    many."""
+    n = (1 << 24) + 12345
+    print("groups", kind, lengths[:5], len(lengths), flush=True)
+    rng = np.random.default_rng(len(lengths))
+    x = rng.integers(-2**63, 2**63, n, dtype=np.int64)
+    at = _unsampled(n, sum(lengths), rng)
+    x[at] = np.repeat(rng.integers(-2**31, 2**31, len(lengths), dtype=np.int64) << 32, lengths)
+    x[at] += rng.integers(0, 2**32, len(at), dtype=np.int64)
+    x[at[:3]] = x[at[0]]                                  # and a few equal ones
+    want = torch.sort(torch.from_numpy(x).to(DEV)).values
+    if kind == "i64":
+        got = hv.sort_keys(torch.from_numpy(x).to(DEV))
+    else:
+        k = torch.from_numpy((x >> 32).astype(np.int32)).to(DEV)
+        v = torch.from_numpy((x & 0xffffffff).astype(np.uint32).view(np.int32) ^ -2**31).to(DEV)
+        ko, vo = hv.sort_pairs(k, v)
+        got = (ko.to(torch.int64) << 32) | ((vo.to(torch.int64) + 2**31) & 0xffffffff)
+    assert torch.equal(got, want)
+
+
+def test_a_long_group_in_order_and_one_out_of_order_at_its_end():
+    n = (1 << 24) + 77
+    rng = np.random.default_rng(4)
+    x = rng.integers(-2**63, 2**63, n, dtype=np.int64)
+    at = np.sort(_unsampled(n, 60000, rng))
+    x[at[:30000]] = 5 << 40                               # equal: always in order
+    x[at[30000:]] = (7 << 40) + np.arange(30000)          # ascending as they stand ...
+    x[at[-1]] = 7 << 40                                   # ... but for the last
+    want = torch.sort(torch.from_numpy(x).to(DEV)).values
+    assert torch.equal(hv.sort_keys(torch.from_numpy(x).to(DEV)), want)
