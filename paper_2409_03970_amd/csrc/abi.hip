@@ -166,9 +166,11 @@ int64_t sort_need(int kind, int64_t n, const Cfg &c, const hvms_options *o)
 {
     const int64_t m =
         sort_ws_layout(n, kind != RADIX_KEYS, c, kind == RADIX_KEYS64).total;
-    const bool digits = radix_route(kind, n, o) ||
-                        (kind == RADIX_PAIRS && radix_route(RADIX_BY_KEY, n, o));
-    const int64_t r = digits ? radix_layout(kind, n).total : 0;
+    int64_t r = radix_route(kind, n, o) ? radix_layout(kind, n).total : 0;
+    if (kind == RADIX_PAIRS && radix_route(RADIX_BY_KEY, n, o)) {
+        const int64_t by_key = radix_layout(RADIX_BY_KEY, n).total - align256(n * 4);
+        r = r > by_key ? r : by_key;
+    }
     return m > r ? m : r;
 }
 

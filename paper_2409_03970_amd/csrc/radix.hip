@@ -989,7 +989,7 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
                 raw_rsrc(a.p[st.src] + base, 8u * (uint32_t)cnt_valid);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                const auto v = __builtin_amdgcn_raw_buffer_load_b64(rp, 8 * e0 + 8 * 64 * k, 0, 0);
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(rp, 8 * e0 + 8 * 64 * k, 0, 2);
                 q[k] = ((uint64_t)(uint32_t)v[1] << 32) | (uint32_t)v[0];
             }
         }
