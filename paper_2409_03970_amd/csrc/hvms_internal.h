@@ -74,6 +74,7 @@ struct RadixArgs {
     uint32_t *sample_pairs; // [run][digit]
     longlong2 *groups;      // first element and length
     int chunks;
+    int sample_runs;
     int round;              // 0, or 1: the passes after radix_finish
     RadixMap map;
     uint32_t fl;

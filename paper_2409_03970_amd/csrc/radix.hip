@@ -21,8 +21,9 @@
 //            LDS and written out in runs.
 // No workgroup waits for another.
 //
-// What bounds a pass (2^28 uniform keys): the count reads 1.07 GB in 0.27 ms
-// (4.0 TB/s, a read-only kernel's rate here).  The scatter takes 0.61 ms for
+// What bounds a pass (2^28 uniform keys): the count reads 1.07 GB in 0.20 ms
+// (5.5 TB/s; 0.27 with loads that fill the memory-side cache on their way).
+// The scatter takes 0.61 ms for
 // 2.15 GB: with its ranks left out and its writes made linear it would take
 // 0.39, with the writes alone linear 0.52, so both the partial cache lines at
 // the ends of the runs and the 55 VALU operations per key (32 of them the
@@ -53,7 +54,7 @@ namespace {
 constexpr int RADIX = 256;
 constexpr int COUNT_NT = 512;
 constexpr int MAX_CHUNKS = 512;
-constexpr int SAMPLE_RUNS = 32, SAMPLE_LEN = 8192, SAMPLE = SAMPLE_RUNS * SAMPLE_LEN;
+constexpr int SAMPLE_LEN = 8192, SAMPLE_RUNS_MAX = 64;
 constexpr int64_t SAMPLE_MIN = (int64_t)1 << 24;  // elements from which a sample is taken
 constexpr int COPIES = 8;  // interleaved histogram copies of the count kernel
 
@@ -146,9 +147,9 @@ template <int KIND> __device__ __forceinline__ Elem load_raw(const RadixArgs &a,
     Elem e{0, 0};
     if constexpr (KIND == RADIX_KEYS64) {
         if (b == B_IN || b == B_OUT) {
-            const uint2 q = ((const uint2 *)a.k[b])[i];
-            e.lo = q.x;
-            e.hi = q.y;
+            const uint64_t q = ((const uint64_t *)a.k[b])[i];
+            e.lo = (uint32_t)q;
+            e.hi = (uint32_t)(q >> 32);
             return e;
         }
     }
@@ -304,6 +305,10 @@ __global__ __launch_bounds__(COUNT_NT) void radix_count(RadixArgs a, int pass)
         hist[i] = 0;
     const int copy = threadIdx.x & (COPIES - 1);
     constexpr bool TWO = KIND == RADIX_PAIRS || KIND == RADIX_KEYS64;
+    // The tiles of keys alone are this large from 2^27 keys, where reading past
+    // the memory-side cache pays (2^27 keys 1.71 -> 1.54 ms, 2^28 3.40 -> 3.21;
+    // 2^25 keys 0.397 -> 0.413, and two-word elements do not care).
+    constexpr bool STREAM = KIND == RADIX_KEYS && T >= 16384;
     const bool low = TWO && pass < 4;
     const int shift = 8 * (pass & 3);
     const uint32_t *p = low ? a.v[st.src] : a.k[st.src];
@@ -314,12 +319,16 @@ __global__ __launch_bounds__(COUNT_NT) void radix_count(RadixArgs a, int pass)
     for (int64_t tile = t0; tile < t1; ++tile) {
         const int64_t lo = tile * T, hi = lo + T < a.n ? lo + T : a.n;
         constexpr int UN = T / (4 * COUNT_NT);
-        uint4 q[UN];
+        typedef uint32_t Words __attribute__((ext_vector_type(4)));
+        Words q[UN];
         const bool full = wide && hi - lo == T;
         if (full) {
 #pragma unroll
             for (int u = 0; u < UN; ++u)
-                q[u] = *(const uint4 *)(p + lo + (u * COUNT_NT + threadIdx.x) * 4);
+{
+                const Words *w = (const Words *)(p + lo) + u * COUNT_NT + threadIdx.x;
+                q[u] = STREAM ? __builtin_nontemporal_load(w) : *w;
+            }
         }
         __syncthreads();
         if (threadIdx.x < RADIX)
@@ -435,7 +444,7 @@ __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64,
     if (threadIdx.x < 8) {  // sampled pairs that first differ in digit threadIdx.x
         uint32_t c = 0;
         if (a.sample)
-            for (int r = 0; r < SAMPLE_RUNS; ++r)
+            for (int r = 0; r < a.sample_runs; ++r)
                 c += a.sample_pairs[r * 8 + threadIdx.x];
         same[threadIdx.x] = c;
     }
@@ -476,16 +485,15 @@ __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64,
         if (two && !keys64 && !(f.flags & VALUES_NOT_ASCENDING))
             need &= 0xf0;
         if (a.sample) {
-            // The most low digits without which hardly any different elements
-            // are alike in the sample: 2^31 values drawn evenly make 0.5 such
-            // pairs of neighbours.  m elements in groups of g make 16 m g
-            // (SAMPLE_LEN / n)^2, so with the three allowed, groups of more
-            // than GROUP_MAX elements slip through only where they are fewer
-            // than one in 10,000.
+            // The most low digits without which the sample leaves an element
+            // alike with at most a quarter of another one on average.  m
+            // elements in groups of g are m g / n of that, so groups of more
+            // than GROUP_MAX elements slip through only where there are few.
+            const double pairs = 0.5 * a.sample_runs * SAMPLE_LEN * SAMPLE_LEN;
             uint32_t alike = 0, drop = 0;
             for (int d = 1; d < 8; ++d) {
                 alike += same[d - 1];
-                if (alike <= 3)
+                if ((double)alike * (double)a.n <= 0.25 * pairs)
                     drop = d;
             }
             const uint32_t low = need & ((1u << drop) - 1);
@@ -551,7 +559,7 @@ __global__ __launch_bounds__(512) void radix_scan(RadixArgs a, int pass, int pas
 // Elements of two words rarely need all their eight digits: once the top ones
 // tell nearly all of them apart, the few that are left alike stand next to
 // each other and are ordered where they are.  How many digits that takes is
-// estimated from a sample sorted in SAMPLE_RUNS runs by the block sort:
+// estimated from a sample sorted in runs by the block sort:
 // neighbours that are equal in the top digits and different below are what a
 // shorter key would leave alike.  The finish checks its own work, so the
 // estimate only costs time where it is wrong: the second round then makes
@@ -605,7 +613,7 @@ __global__ __launch_bounds__(256) void radix_sample_pairs(RadixArgs a)
 // elements (2^28 uniform pairs, 12 % of them alike: 2.5 ms when the first
 // lane of each group read it through in memory, now 1.0).
 constexpr int GROUP_MAX = 8192;    // elements of a listed group: one block-sort tile
-constexpr int GROUPS_MAX = 16384;  // listed groups
+constexpr int GROUPS_MAX = 65536;  // listed groups
 
 template <int KIND> __device__ __forceinline__ uint64_t finish_elem(const RadixArgs &a, int64_t i)
 {
@@ -1119,6 +1127,13 @@ int chunk_log2(int64_t tiles)
 
 }  // namespace
 
+// Runs of the sample, sorted a run to a CU: 2^18 or 2^19 elements.
+static int sample_runs(int64_t n)
+{
+    const int64_t r = n >> 19;
+    return (int)(r < SAMPLE_RUNS_MAX ? r : SAMPLE_RUNS_MAX);
+}
+
 RadixLayout radix_layout(int kind, int64_t n)
 {
     RadixLayout w{};
@@ -1154,9 +1169,9 @@ RadixLayout radix_layout(int kind, int64_t n)
     off += align256(tiles * RADIX * 4);
     if ((kind == RADIX_PAIRS || kind == RADIX_KEYS64) && n >= SAMPLE_MIN) {
         w.sample = off;
-        off += SAMPLE * 8;
+        off += (int64_t)sample_runs(n) * SAMPLE_LEN * 8;
         w.sample_pairs = off;
-        off += SAMPLE_RUNS * 8 * 4;
+        off += sample_runs(n) * 8 * 4;
         w.groups = off;
         off += GROUPS_MAX * (int64_t)sizeof(longlong2);
     }
@@ -1180,15 +1195,16 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
     wg = (wg + 7) & ~(int64_t)7;
     const dim3 cgrid((unsigned)a.chunks), sgrid((unsigned)wg);
     if (a.sample) {
-        hipLaunchKernelGGL(radix_sample<KIND>, dim3(SAMPLE / 256), dim3(256), 0, s, a);
+        const int64_t samples = (int64_t)a.sample_runs * SAMPLE_LEN;
+        hipLaunchKernelGGL(radix_sample<KIND>, dim3((unsigned)(samples / 256)), dim3(256), 0, s, a);
         KeyMap packed;
         packed.packed = true;
         const hipError_t e = launch_block_sort(8, 1024, true, (const int32_t *)a.sample, nullptr,
-                                               (int32_t *)a.sample, nullptr, SAMPLE, 6, 4, false,
+                                               (int32_t *)a.sample, nullptr, samples, 6, 4, false,
                                                s, 0, packed, packed);
         if (e != hipSuccess)
             return e;
-        hipLaunchKernelGGL(radix_sample_pairs, dim3(SAMPLE_RUNS), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(radix_sample_pairs, dim3(a.sample_runs), dim3(256), 0, s, a);
     }
     for (int p = 0; p < passes; ++p) {
         if (p == 0)
@@ -1244,6 +1260,7 @@ hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap
     a.rows = (uint32_t *)(base + w.rows);
     if (w.sample) {
         a.sample = (uint64_t *)(base + w.sample);
+        a.sample_runs = sample_runs(n);
         a.sample_pairs = (uint32_t *)(base + w.sample_pairs);
         a.groups = (longlong2 *)(base + w.groups);
     }

@@ -153,7 +153,7 @@ def test_arrays_off_the_16_byte_grid():
 
 def _unsampled(n, count, rng):
     """Positions that the sample of the digit choice does not read: element j
-    of its 2^18 is at SplitMix64(j) * n / 2^64."""
+    of its 2^18 (at fewer than 2^25 elements) is at SplitMix64(j) * n / 2^64."""
     with np.errstate(over="ignore"):
         z = (np.arange(1 << 18, dtype=np.uint64) + np.uint64(1)) * np.uint64(0x9E3779B97F4A7C15)
         z = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
@@ -168,7 +168,7 @@ def _unsampled(n, count, rng):
 
 @pytest.mark.parametrize("lengths", [tuple(range(2, 70)), (31, 32, 33, 34, 63, 64, 65, 66) * 20,
                                      (100, 1000, 8190, 8191, 8192), (8193,), (8256, 8447, 8449),
-                                     (20000,), (2,) * 30000, (40,) * 16385])
+                                     (20000,), (2,) * 30000, (40,) * 65537])
 @pytest.mark.parametrize("kind", ("i64", "pairs"))
 def test_groups_left_alike_by_the_top_digits(lengths, kind):
     """Groups that share their upper words, planted where the sample does not
