@@ -138,8 +138,8 @@ int hvms_last_hip_error(void);
 /*
  * Calls whose options leave everything to the library (NULL, or every field
  * 0) sort large arrays by stable passes over 8-bit digits instead of merge
- * passes: keys alone and sorts by key from 2^16 keys, pairs and 64-bit keys
- * from 2^22 to 3 * 2^24.  The result is the same bit for bit.  Any option set
+ * passes: keys alone and sorts by key past 2^15 keys, pairs and 64-bit keys
+ * from 2^22.  The result is the same bit for bit.  Any option set
  * (a tile shape, a co-rank mode, stats, events, ...) keeps the merge sort, and
  * so does a workspace that only holds what the merge sort needs.
  */

@@ -458,7 +458,7 @@ def hvms_cdf_sample_i32(keys, m, seed, out, stream=None):
 
 # sizes from which the library's own choice (digit passes) beats every merge
 # shape, so no tuned shape is asked for: first and last n of each kind of sort
-_DIGIT_PASSES = {"sort": (1 << 16, 2**32 - 2**16), "sort_by_key": (1 << 16, 2**31 - 1),
+_DIGIT_PASSES = {"sort": (2**15 + 1, 2**32 - 2**16), "sort_by_key": (2**15 + 1, 2**31 - 1),
                  "sort_pairs": (1 << 22, 2**32 - 2**16)}
 
 

@@ -143,20 +143,17 @@ bool library_choice(const hvms_options *o)
 }
 
 // Sizes that take the digit passes (radix.hip) where the choice is the
-// library's.  Keys alone and the sort by key: from 2^16 keys, where their
-// twelve launches meet the merge sort's (2^15 uniform keys 47 against 37 us,
-// 2^16 46 against 50, 2^20 64 against 109, 2^28 3.4 against 5.7 ms).  Two-word
-// elements make up to eight passes: from 2^22 (pairs of any order there 0.21
-// against 0.25-0.31 ms; at 2^21 presorted keys are even) up to 3 * 2^24, past
-// which their runs go to HBM in pieces and random pairs lose (2^25 1.23 against
-// 1.69 ms, 2^26 2.78 against 2.60).
-constexpr int64_t kRadixMin = 1 << 16, kRadixMin2 = 1 << 22, kRadixMax2 = ((int64_t)1 << 32) - (1 << 16);
+// library's.  Keys alone and the sort by key: past 2^15 keys, where the merge
+// sort takes its third merge level (2^15 uniform keys 38 against 37 us, 2^16 42
+// against 50, 2^20 64 against 109, 2^28 3.2 against 5.7 ms).  Two-word elements
+// make up to eight passes: from 2^22 (pairs of any order there 0.21 against
+// 0.25-0.31 ms; at 2^21 presorted keys are even).
+constexpr int64_t kRadixMin = (1 << 15) + 1, kRadixMin2 = 1 << 22;
 constexpr int64_t kRadixMax = ((int64_t)1 << 32) - (1 << 16);  // 32-bit positions
 bool radix_route(int kind, int64_t n, const hvms_options *o)
 {
     const bool two = kind == RADIX_PAIRS || kind == RADIX_KEYS64;
-    return n >= (two ? kRadixMin2 : kRadixMin) && n <= (two ? kRadixMax2 : kRadixMax) &&
-           library_choice(o);
+    return n >= (two ? kRadixMin2 : kRadixMin) && n <= kRadixMax && library_choice(o);
 }
 
 // Workspace of a sort by either route.  A pair sort's has room for the digit

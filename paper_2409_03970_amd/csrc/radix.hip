@@ -54,6 +54,7 @@ namespace {
 constexpr int RADIX = 256;
 constexpr int COUNT_NT = 512;
 constexpr int MAX_CHUNKS = 512;
+constexpr int FEW_TILES = 32;
 constexpr int SAMPLE_LEN = 8192, SAMPLE_RUNS_MAX = 64;
 constexpr int64_t SAMPLE_MIN = (int64_t)1 << 24;  // elements from which a sample is taken
 constexpr int COPIES = 8;  // interleaved histogram copies of the count kernel
@@ -74,18 +75,21 @@ struct Ctl {
 };
 
 // The step of a pass, in scalar registers.
-__device__ __forceinline__ Step step_of(const RadixArgs &a, int pass)
+__device__ __forceinline__ Step step_of(const Ctl *ctl, int round, int pass)
 {
-    const Ctl *ctl = (const Ctl *)a.ctl;
-    const uint32_t *q = (const uint32_t *)&ctl->step[a.round][pass];
+    const uint32_t *q = (const uint32_t *)&ctl->step[round][pass];
     Step s;
-    s.mode = a.round == 0 || ctl->again ? q[0] : (uint32_t)STEP_SKIP;
+    s.mode = round == 0 || ctl->again ? q[0] : (uint32_t)STEP_SKIP;
     s.mode = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.mode);
     s.src = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[1]);
     s.dst = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[2]);
     s.first = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[3]);
     s.last = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[4]);
     return s;
+}
+__device__ __forceinline__ Step step_of(const RadixArgs &a, int pass)
+{
+    return step_of((const Ctl *)a.ctl, a.round, pass);
 }
 
 // What one chunk's count says about the input's order (flag set = not so).
@@ -419,14 +423,16 @@ __device__ void scatter_modes(uint32_t *mode, uint32_t need, int passes, bool ke
             }
 }
 
-// The steps of the sort from what the chunks found (one workgroup).
-__device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64, bool inplace)
+// The steps of the sort from what the chunks found, by one workgroup of at
+// most 512 threads (ctl: where they go, in LDS or memory).
+__device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64, bool inplace,
+                          Ctl *ctl)
 {
     __shared__ ChunkInfo part[8];
     __shared__ uint32_t same[8];
     ChunkInfo f{~0u, 0u, ~0u, 0u, 0u, {0, 0, 0}};
     const ChunkInfo *info = (const ChunkInfo *)a.info;
-    for (int c = threadIdx.x; c < a.chunks; c += 512) {
+    for (int c = threadIdx.x; c < a.chunks; c += blockDim.x) {
         const ChunkInfo g = info[c];
         f.and0 &= g.and0;
         f.or0 |= g.or0;
@@ -451,14 +457,13 @@ __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64,
     __syncthreads();
     if (threadIdx.x != 0)
         return;
-    for (int w = 1; w < 8; ++w) {
+    for (int w = 1; w < (int)blockDim.x / 64; ++w) {
         f.and0 &= part[w].and0;
         f.or0 |= part[w].or0;
         f.and1 &= part[w].and1;
         f.or1 |= part[w].or1;
         f.flags |= part[w].flags;
     }
-    Ctl *ctl = (Ctl *)a.ctl;
     uint32_t mode[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     const bool ascending = !(f.flags & NOT_ASCENDING);
     const bool descending = !(f.flags & NOT_DESCENDING);
@@ -517,7 +522,7 @@ __global__ __launch_bounds__(512) void radix_scan(RadixArgs a, int pass, int pas
                                                   int keys64, int inplace)
 {
     if (blockIdx.x == RADIX / 16) {
-        make_plan(a, passes, two != 0, keys64 != 0, inplace != 0);
+        make_plan(a, passes, two != 0, keys64 != 0, inplace != 0, (Ctl *)a.ctl);
         return;
     }
     if ((pass > 0 || a.round) && step_of(a, pass).mode != STEP_SCATTER)
@@ -805,8 +810,12 @@ __device__ __forceinline__ void copy_step(const RadixArgs &a, const Step &st)
     }
 }
 
-template <int NT, int K, int KIND, int WAVES>
-__global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass)
+//
+// FEW (one workgroup to a tile, at most FEW_TILES tiles): no scan launch.
+// Every workgroup adds up the tiles' counts itself, and in the first pass
+// makes the plan.
+template <int NT, int K, int KIND, int WAVES, bool FEW>
+__global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass, int inplace)
 {
     constexpr int T = NT * K;
     constexpr int NW = NT / 64;
@@ -822,7 +831,19 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
     __shared__ __align__(16) uint32_t gpre[RADIX];     // output index of the tile's first such key
     uint32_t *xch = (uint32_t *)xraw;
 
-    const Step st = step_of(a, pass);
+    Step st;
+    if (FEW && pass == 0) {
+        __shared__ Ctl plan;
+        make_plan(a, 4, false, false, inplace != 0, &plan);
+        __syncthreads();
+        st = step_of(&plan, 0, 0);
+        if (blockIdx.x == 0) {
+            for (int i = threadIdx.x; i < (int)(sizeof(Ctl) / 4); i += NT)
+                ((uint32_t *)a.ctl)[i] = ((const uint32_t *)&plan)[i];
+        }
+    } else {
+        st = step_of(a, pass);
+    }
     if (st.mode == STEP_SKIP)
         return;
     if (st.mode != STEP_SCATTER) {
@@ -841,10 +862,51 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
     uint32_t *wdst = low ? a.v[st.dst] : a.k[st.dst];
     uint32_t *sdst = low ? a.k[st.dst] : a.v[st.dst];
 
-    // thread t < 256: where digit t's region of the output starts
+    // An XCD's workgroups (every eighth one) walk one contiguous range of
+    // tiles together, so that the lines two neighbouring tiles share are
+    // completed in that XCD's L2.
+    const int slots = FEW ? (int)a.tiles : (int)gridDim.x >> 3;
+    const int64_t xcd = blockIdx.x & 7;
+    const int64_t tile1 = FEW ? a.tiles : (xcd + 1) * a.tiles >> 3;
+    int64_t tile = FEW ? (int64_t)blockIdx.x : (xcd * a.tiles >> 3) + (blockIdx.x >> 3);
+
+    // thread t < 256: where digit t's region of the output starts (FEW: this
+    // tile's part of it)
     uint32_t region = 0;
+    if constexpr (FEW) {
+        // thread d + 256 h: digit d over every (NT / 256)th tile from tile h
+        constexpr int H = NT / RADIX, U = 16;
+        uint32_t *sums = xch;  // [h][digit]: all tiles', then the ones before
+        uint32_t all = 0, mine = 0;
+        for (int c0 = tid / RADIX; c0 < (int)a.tiles; c0 += U * H) {
+            uint32_t v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                v[u] = c0 + u * H < (int)a.tiles
+                           ? a.counts[(c0 + u * H) * RADIX + (tid & (RADIX - 1))]
+                           : 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                all += v[u];
+                mine += c0 + u * H < (int)tile ? v[u] : 0;
+            }
+        }
+        sums[tid] = all;
+        sums[NT + tid] = mine;
+        __syncthreads();
+        if (tid < RADIX) {
+            all = 0;
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                all += sums[h * RADIX + tid];
+                region += sums[NT + h * RADIX + tid];
+            }
+            gbase[tid] = all;
+        }
+        __syncthreads();
+    }
     if (wave == 0) {
-        const uint4 t = *(const uint4 *)(a.totals + 4 * lane);
+        const uint4 t = *(const uint4 *)((FEW ? gbase : a.totals) + 4 * lane);
         const uint32_t s = t.x + t.y + t.z + t.w;
         const uint32_t ex = wave_inclusive(s) - s;
         *(uint4 *)&gpre[4 * lane] =
@@ -852,15 +914,8 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
     }
     __syncthreads();
     if (tid < RADIX)
-        region = gpre[tid];
+        region += gpre[tid];
 
-    // An XCD's workgroups (every eighth one) walk one contiguous range of
-    // tiles together, so that the lines two neighbouring tiles share are
-    // completed in that XCD's L2.
-    const int slots = (int)gridDim.x >> 3;
-    const int64_t xcd = blockIdx.x & 7;
-    const int64_t tile1 = (xcd + 1) * a.tiles >> 3;
-    int64_t tile = (xcd * a.tiles >> 3) + (blockIdx.x >> 3);
     // Loads of a tile's words through buffer resources: they end at the
     // array's last element (zeros past it) and take one lane offset and
     // constant row offsets.  hi: which word of a packed array.
@@ -886,7 +941,7 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
         const int64_t base = tile * T;
         const int cnt_valid = a.n - base < T ? (int)(a.n - base) : T;
         uint32_t first = region;
-        if (tid < RADIX)
+        if (!FEW && tid < RADIX)
             first += a.rows[tile * RADIX + tid] + a.counts[(tile >> a.per_log2) * RADIX + tid];
         int t0 = tid;
         asm("" : "+v"(t0));  // keeps the row offsets out of registers held across tiles
@@ -1093,16 +1148,19 @@ constexpr int64_t align256(int64_t b) { return (b + 255) & ~(int64_t)255; }
 struct Shape {
     int nt, k;
 };
-constexpr Shape SHAPES[] = {{256, 8}, {512, 16}, {512, 32}, {1024, 16}};
+constexpr Shape SHAPES[] = {{256, 8}, {512, 16}, {512, 32}, {1024, 16}, {512, 8}};
 
 // Small sorts take small tiles (more workgroups than 8,192-key tiles give:
-// 2^20 keys 66 against 71 us, 2^22 keys 96 and 97), keys alone large ones once
+// 2^20 keys 66 against 71 us, 2^22 keys 96 and 97), up to 2^17 keys such that
+// there are at most FEW_TILES (32) of them, whose sums cost a workgroup less
+// than the scan launch (2^16 keys 51 -> 42 us, 100,003 keys 53 -> 43; 64 tiles
+// of 2,048 keys 52 -> 50, 128 52 -> 64); keys alone large ones once
 // the runs go to HBM (2^26 keys 0.78 against 0.80 ms, 2^28 keys 3.78 against
 // 3.40).  Two words a key at K = 32 would spill.
 int shape_of(int kind, int64_t n)
 {
     if (n < ((int64_t)1 << 22))
-        return 0;
+        return n > ((int64_t)1 << 16) && n <= ((int64_t)1 << 17) ? 4 : 0;
     if (kind == RADIX_KEYS)
         return n >= ((int64_t)1 << 27) ? 2 : 1;
     return kind != RADIX_BY_KEY && n >= ((int64_t)1 << 26) ? 3 : 1;
@@ -1190,6 +1248,20 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
     a.tiles = (a.n + T - 1) / T;
     a.per_log2 = chunk_log2(a.tiles);
     a.chunks = (int)((a.tiles + ((int64_t)1 << a.per_log2) - 1) >> a.per_log2);
+    if constexpr (SHAPE == 0 || SHAPE == 4) {
+        if (a.tiles <= FEW_TILES) {
+            const dim3 grid((unsigned)a.tiles);
+            for (int p = 0; p < passes; ++p) {
+                if (p == 0)
+                    hipLaunchKernelGGL((radix_count_first<KIND, T>), grid, dim3(COUNT_NT), 0, s, a);
+                else
+                    hipLaunchKernelGGL((radix_count<KIND, T>), grid, dim3(COUNT_NT), 0, s, a, p);
+                hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, true>), grid, dim3(NT), 0, s,
+                                   a, p, (int)inplace);
+            }
+            return hipGetLastError();
+        }
+    }
     const int64_t fit = (int64_t)device_cus() * WGS;
     int64_t wg = a.tiles < fit ? a.tiles : fit;
     wg = (wg + 7) & ~(int64_t)7;
@@ -1213,7 +1285,8 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
             hipLaunchKernelGGL((radix_count<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a, p);
         hipLaunchKernelGGL(radix_scan, dim3(RADIX / 16 + (p == 0)), dim3(512), 0, s, a, p, passes,
                            (int)two, (int)keys64, (int)inplace);
-        hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES>), sgrid, dim3(NT), 0, s, a, p);
+        hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, false>), sgrid, dim3(NT), 0, s, a, p,
+                           (int)inplace);
     }
     if constexpr (two) {
         if (a.sample) {
@@ -1227,8 +1300,8 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
                 hipLaunchKernelGGL((radix_count<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a, p);
                 hipLaunchKernelGGL(radix_scan, dim3(RADIX / 16), dim3(512), 0, s, a, p, passes,
                                    (int)two, (int)keys64, 1);
-                hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES>), sgrid, dim3(NT), 0, s, a,
-                                   p);
+                hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, false>), sgrid, dim3(NT), 0,
+                                   s, a, p, 1);
             }
         }
     }
@@ -1273,20 +1346,22 @@ hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap
     switch (kind) {
     case RADIX_KEYS:
         return shape == 0   ? run_radix<RADIX_KEYS, 0, 6, 6>(a, inplace, s)
+               : shape == 4 ? run_radix<RADIX_KEYS, 4, 6, 3>(a, inplace, s)
                : shape == 1 ? run_radix<RADIX_KEYS, 1, 6, 3>(a, inplace, s)
                             : run_radix<RADIX_KEYS, 2, 4, 2>(a, inplace, s);
     case RADIX_PAIRS:
-        if (shape == 0)
+        if (shape == 0 || shape == 4)
             break;
         return shape == 3 ? run_radix<RADIX_PAIRS, 3, 4, 1>(a, inplace, s)
                           : run_radix<RADIX_PAIRS, 1, 4, 2>(a, inplace, s);
     case RADIX_KEYS64:
-        if (shape == 0)
+        if (shape == 0 || shape == 4)
             break;
         return shape == 3 ? run_radix<RADIX_KEYS64, 3, 4, 1>(a, inplace, s)
                           : run_radix<RADIX_KEYS64, 1, 4, 2>(a, inplace, s);
     case RADIX_BY_KEY:
-        return shape == 0 ? run_radix<RADIX_BY_KEY, 0, 4, 4>(a, inplace, s)
+        return shape == 0   ? run_radix<RADIX_BY_KEY, 0, 4, 4>(a, inplace, s)
+               : shape == 4 ? run_radix<RADIX_BY_KEY, 4, 4, 2>(a, inplace, s)
                           : run_radix<RADIX_BY_KEY, 1, 4, 2>(a, inplace, s);
     }
     return hipErrorInvalidValue;

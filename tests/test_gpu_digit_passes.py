@@ -22,8 +22,9 @@ def _keys(n, dist, seed=0):
     return inputs.adversarial_keys(n, dist, seed=seed, device=DEV)
 
 
-@pytest.mark.parametrize("n", [1 << 16, (1 << 16) + 1, 2048 * 37 - 1, 100003, (1 << 19) + 2049,
-                               (1 << 22) - 1, 1 << 22, 8192 * 1025 + 1])
+@pytest.mark.parametrize("n", [(1 << 15) + 1, 2048 * 31 + 1, 1 << 16, (1 << 16) + 1, 100003,
+                               1 << 17, (1 << 17) + 1, (1 << 19) + 2049, (1 << 22) - 1, 1 << 22,
+                               8192 * 1025 + 1])
 @pytest.mark.parametrize("dist", KEYS)
 def test_keys_and_in_place(n, dist):
     print("digit passes", n, dist, flush=True)
@@ -54,7 +55,8 @@ def test_mapped_keys(dtype):
     assert np.array_equal(got, ref.view(np.uint32))
 
 
-@pytest.mark.parametrize("n", [1 << 16, 2048 * 33 + 1, (1 << 22) + 8191])
+@pytest.mark.parametrize("n", [(1 << 15) + 1, 1 << 16, 2048 * 33 + 1, 1 << 17, 2048 * 65,
+                               (1 << 22) + 8191])
 @pytest.mark.parametrize("dist", ("uniform", "sorted", "reverse", "distinct16", "zipf", "equal"))
 def test_by_key(n, dist):
     print("by key", n, dist, flush=True)
