@@ -40,7 +40,8 @@
 // The first count also finds which bits vary and whether the input is
 // already in order (or in reverse order).  From that one workgroup of the
 // first scan launch makes the plan of the sort: passes over constant digits
-// are skipped and presorted input is copied (sorted 2^28 keys 0.83 ms).  A
+// are skipped and presorted input is copied (sorted 2^28 keys 0.67 ms, of which
+// the copy 0.44; 1.01 with one key to a thread in flight in both).  A
 // pair sort whose values ascend in the input skips its value digits, since
 // stable passes over the key alone then give the lexicographic order.
 // Skipped launches return at once; nothing is read back by the host.
@@ -204,6 +205,89 @@ __device__ __forceinline__ uint32_t hist_sum(const uint32_t *hist, int d)
     return s;
 }
 
+typedef uint32_t Words __attribute__((ext_vector_type(4)));
+
+// A whole tile from element i0 on for the first count; the caller's arrays are
+// 16-byte aligned, and `more` if an element follows the tile.  A lane takes the
+// consecutive elements of one load, so that all but one of their comparisons
+// with the element after need no other lane: the first count reads 2^28 keys
+// in 0.21 ms, as the others do (0.27 with one key to a lane and load).
+template <int KIND, int T>
+__device__ __forceinline__ void count_first_tile(const RadixArgs &a, int64_t i0, bool more,
+                                                 ChunkInfo &f, uint32_t *hist)
+{
+    constexpr bool TWO = KIND == RADIX_PAIRS || KIND == RADIX_KEYS64;
+    constexpr bool STREAM = KIND == RADIX_KEYS && T >= 16384;
+    constexpr int NE = KIND == RADIX_KEYS64 ? 2 : 4;  // elements of a load
+    constexpr int LOADS = T / (NE * COUNT_NT);
+    constexpr int UN = LOADS < (KIND == RADIX_PAIRS ? 4 : 8) ? LOADS : KIND == RADIX_PAIRS ? 4 : 8;
+    const int lane = lane_id(), copy = lane & (COPIES - 1);
+    const uint32_t *pk = a.k[B_IN] + (KIND == RADIX_KEYS64 ? 2 : 1) * i0;
+    const uint32_t *pv = KIND == RADIX_PAIRS ? a.v[B_IN] + i0 : nullptr;
+    bool gt = false, lt = false, vgt = false;
+#pragma unroll 1
+    for (int u0 = 0; u0 < LOADS; u0 += UN) {
+        Words q[UN], v[UN];
+        Elem after[UN];  // the element after the wave's
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int at = (u0 + u) * COUNT_NT + threadIdx.x;
+            const Words *w = (const Words *)pk + at;
+            q[u] = STREAM ? __builtin_nontemporal_load(w) : *w;
+            if constexpr (KIND == RADIX_PAIRS)
+                v[u] = ((const Words *)pv)[at];
+            const int e = NE * ((u0 + u) * COUNT_NT + (int)(threadIdx.x & ~63u) + 64);
+            after[u] = load_raw<KIND>(a, B_IN, i0 + (e < T || more ? e : T - 1));
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            Elem k[NE + 1];
+#pragma unroll
+            for (int j = 0; j < NE; ++j) {
+                if constexpr (KIND == RADIX_KEYS64)
+                    k[j] = Elem{q[u][2 * j + 1], q[u][2 * j]};
+                else if constexpr (KIND == RADIX_PAIRS)
+                    k[j] = Elem{q[u][j], v[u][j]};
+                else
+                    k[j] = Elem{q[u][j], 0};
+                k[j] = map_elem2<KIND>(k[j], a);
+            }
+            after[u] = map_elem2<KIND>(after[u], a);
+            k[NE].hi = (uint32_t)__shfl_down((int)k[0].hi, 1);
+            k[NE].hi = lane == 63 ? after[u].hi : k[NE].hi;
+            if constexpr (TWO) {
+                k[NE].lo = (uint32_t)__shfl_down((int)k[0].lo, 1);
+                k[NE].lo = lane == 63 ? after[u].lo : k[NE].lo;
+            }
+            // the array's last element has none after it
+            const bool end = !more && u0 + u == LOADS - 1 && threadIdx.x == COUNT_NT - 1;
+#pragma unroll
+            for (int j = 0; j < NE; ++j) {
+                bool g = k[j].hi > k[j + 1].hi;
+                // a stable sort may reverse only where no two keys are equal
+                bool l = KIND == RADIX_BY_KEY ? k[j].hi <= k[j + 1].hi : k[j].hi < k[j + 1].hi;
+                if constexpr (TWO) {
+                    const bool eq = k[j].hi == k[j + 1].hi;
+                    g = g || (eq && k[j].lo > k[j + 1].lo);
+                    l = l || (eq && k[j].lo < k[j + 1].lo);
+                    if constexpr (KIND == RADIX_PAIRS)
+                        vgt = vgt || k[j].lo > k[j + 1].lo;
+                    f.and0 &= k[j].lo;
+                    f.or0 |= k[j].lo;
+                }
+                gt = gt || g;
+                lt = lt || (l && !(j == NE - 1 && end));
+                f.and1 &= k[j].hi;
+                f.or1 |= k[j].hi;
+                const uint32_t w = TWO ? k[j].lo : k[j].hi;
+                atomicAdd(&hist[(w & 255) * COPIES + copy], 1u);
+            }
+        }
+    }
+    f.flags |= (gt ? NOT_ASCENDING : 0) | (lt ? NOT_DESCENDING : 0) |
+               (vgt ? VALUES_NOT_ASCENDING : 0);
+}
+
 // Pass 0: the histogram of digit 0 and what the plan needs to know.
 template <int KIND, int T>
 __global__ __launch_bounds__(COUNT_NT) void radix_count_first(RadixArgs a)
@@ -218,6 +302,8 @@ __global__ __launch_bounds__(COUNT_NT) void radix_count_first(RadixArgs a)
     // element 64 r + l, and the next element comes from the next lane
     constexpr int UN = KIND == RADIX_KEYS ? 8 : 4;
     constexpr int STEP = COUNT_NT * UN;
+    const bool wide = (((uintptr_t)a.k[B_IN] | (KIND == RADIX_PAIRS ? (uintptr_t)a.v[B_IN] : 0)) &
+                       15) == 0;
     const int64_t t0 = (int64_t)blockIdx.x << a.per_log2;
     const int64_t t1 = min(t0 + ((int64_t)1 << a.per_log2), a.tiles);
     for (int64_t tile = t0; tile < t1; ++tile) {
@@ -226,6 +312,10 @@ __global__ __launch_bounds__(COUNT_NT) void radix_count_first(RadixArgs a)
             a.rows[tile * RADIX + threadIdx.x] = hist_sum(hist, threadIdx.x);
         __syncthreads();
         const int64_t hi = (tile + 1) * T < a.n ? (tile + 1) * T : a.n;
+        if (wide && hi - tile * T == T) {
+            count_first_tile<KIND, T>(a, tile * T, hi < a.n, f, hist);
+            continue;
+        }
         for (int64_t base = tile * T + (int64_t)(threadIdx.x / 64) * (64 * UN); base < hi;
              base += STEP) {
             Elem e[UN + 1];
@@ -317,45 +407,66 @@ __global__ __launch_bounds__(COUNT_NT) void radix_count(RadixArgs a, int pass)
     const int shift = 8 * (pass & 3);
     const uint32_t *p = low ? a.v[st.src] : a.k[st.src];
     // st.first: the caller's array, unmapped (the passes before were skipped)
-    const bool wide = !st.first && ((uintptr_t)p & 15) == 0;
+    const bool packed = KIND == RADIX_KEYS64 && st.first;
+    const bool wide = ((uintptr_t)(packed ? a.k[st.src] : p) & 15) == 0;
+    auto add = [&](uint32_t w) { atomicAdd(&hist[((w >> shift) & 255) * COPIES + copy], 1u); };
     const int64_t t0 = (int64_t)blockIdx.x << a.per_log2;
     const int64_t t1 = min(t0 + ((int64_t)1 << a.per_log2), a.tiles);
     for (int64_t tile = t0; tile < t1; ++tile) {
         const int64_t lo = tile * T, hi = lo + T < a.n ? lo + T : a.n;
         constexpr int UN = T / (4 * COUNT_NT);
-        typedef uint32_t Words __attribute__((ext_vector_type(4)));
         Words q[UN];
         const bool full = wide && hi - lo == T;
+        const Words *w = (const Words *)(packed ? a.k[st.src] + 2 * lo : p + lo) + threadIdx.x;
         if (full) {
 #pragma unroll
             for (int u = 0; u < UN; ++u)
-{
-                const Words *w = (const Words *)(p + lo) + u * COUNT_NT + threadIdx.x;
-                q[u] = STREAM ? __builtin_nontemporal_load(w) : *w;
-            }
+                q[u] = STREAM ? __builtin_nontemporal_load(w + u * COUNT_NT) : w[u * COUNT_NT];
         }
         __syncthreads();
         if (threadIdx.x < RADIX)
             a.rows[tile * RADIX + threadIdx.x] = hist_sum(hist, threadIdx.x);
         __syncthreads();
-        if (full) {
+        if (full && !st.first) {
 #pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                atomicAdd(&hist[((q[u].x >> shift) & 255) * COPIES + copy], 1u);
-                atomicAdd(&hist[((q[u].y >> shift) & 255) * COPIES + copy], 1u);
-                atomicAdd(&hist[((q[u].z >> shift) & 255) * COPIES + copy], 1u);
-                atomicAdd(&hist[((q[u].w >> shift) & 255) * COPIES + copy], 1u);
+            for (int u = 0; u < UN; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    add(q[u][j]);
+        } else if (full && !packed) {
+#pragma unroll
+            for (int u = 0; u < UN; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    add(KIND == RADIX_PAIRS && low ? q[u][j] ^ 0x80000000u
+                                                   : map_key(q[u][j], a.map));
+        } else if (full) {
+            // two elements to a load: the tile's second half follows
+#pragma unroll 1
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int u = 0; u < UN; ++u) {
+                    if (h)
+                        q[u] = w[(UN + u) * COUNT_NT];
+                }
+#pragma unroll
+                for (int u = 0; u < UN; ++u)
+#pragma unroll
+                    for (int j = 0; j < 4; j += 2) {
+                        const Elem e = map_elem2<KIND>(Elem{q[u][j + 1], q[u][j]}, a);
+                        add(low ? e.lo : e.hi);
+                    }
             }
         } else {
             for (int64_t i = lo + threadIdx.x; i < hi; i += COUNT_NT) {
-                uint32_t w;
+                uint32_t x;
                 if (st.first) {
                     const Elem e = map_elem2<KIND>(load_raw<KIND>(a, st.src, i), a);
-                    w = low ? e.lo : e.hi;
+                    x = low ? e.lo : e.hi;
                 } else {
-                    w = p[i];
+                    x = p[i];
                 }
-                atomicAdd(&hist[((w >> shift) & 255) * COPIES + copy], 1u);
+                add(x);
             }
         }
     }
@@ -794,19 +905,37 @@ __device__ __forceinline__ void match_digit(uint32_t d, uint32_t &lo, uint32_t &
     }
 }
 
-template <int NT, int KIND>
+// Copies the input (or reverses it); UN elements to a thread in flight, since
+// the scatter's LDS leaves few waves on a CU.
+template <int NT, int KIND, int UN>
 __device__ __forceinline__ void copy_step(const RadixArgs &a, const Step &st)
 {
-    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < a.n; i += (int64_t)gridDim.x * NT) {
-        const int64_t o = st.mode == STEP_REVERSE ? a.n - 1 - i : i;
-        Elem e = load_raw<KIND>(a, st.src, i);
-        if (st.first)
-            e = map_elem2<KIND>(e, a);
-        if (st.last)
-            e = unmap_elem2<KIND>(e, a);
-        store_raw<KIND>(a, st.dst, o, e);
-        if constexpr (KIND == RADIX_BY_KEY)
-            a.p[st.dst][o] = a.p[st.src][i];
+    for (int64_t i0 = (int64_t)blockIdx.x * (NT * UN); i0 < a.n;
+         i0 += (int64_t)gridDim.x * (NT * UN)) {
+        Elem e[UN];
+        uint64_t pay[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int64_t i = i0 + u * NT + threadIdx.x;
+            const int64_t c = i < a.n ? i : a.n - 1;
+            e[u] = load_raw<KIND>(a, st.src, c);
+            if constexpr (KIND == RADIX_BY_KEY)
+                pay[u] = a.p[st.src][c];
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int64_t i = i0 + u * NT + threadIdx.x;
+            const int64_t o = st.mode == STEP_REVERSE ? a.n - 1 - i : i;
+            if (st.first)
+                e[u] = map_elem2<KIND>(e[u], a);
+            if (st.last)
+                e[u] = unmap_elem2<KIND>(e[u], a);
+            if (i < a.n) {
+                store_raw<KIND>(a, st.dst, o, e[u]);
+                if constexpr (KIND == RADIX_BY_KEY)
+                    a.p[st.dst][o] = pay[u];
+            }
+        }
     }
 }
 
@@ -847,7 +976,7 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
     if (st.mode == STEP_SKIP)
         return;
     if (st.mode != STEP_SCATTER) {
-        copy_step<NT, KIND>(a, st);
+        copy_step<NT, KIND, (K >= 32 ? 8 : 4)>(a, st);
         return;
     }
     const int tid = threadIdx.x, lane = lane_id();

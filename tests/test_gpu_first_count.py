@@ -1,0 +1,87 @@
+"""The first count of the digit passes and the counts that read the caller's
+array: a single pair of elements out of order at the edges of a lane's load, a
+wave, a tile and the array must not pass for presorted input, and passes whose
+lower digits are constant count the caller's words, on and off the 16-byte
+grid, with and without a ragged last tile."""
+import pytest
+import torch
+
+import paper_2409_03970_amd as hv
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+KINDS = ("keys", "by_key", "pairs", "i64")
+EDGES = (0, 1, 3, 63, 127, 255, 1023, 2047, 4095, 8191, 16383)
+
+
+def _off(x, off):
+    """x at `off` elements past an allocation's start."""
+    buf = torch.empty(x.numel() + 8, dtype=x.dtype, device=DEV)
+    view = buf[off:off + x.numel()]
+    view.copy_(x)
+    return view
+
+
+def _check(kind, words, off, what):
+    """Sorts `words` (int64) by the kind's entry point against torch."""
+    n = words.numel()
+    idx = torch.arange(n, device=DEV)
+    if kind == "i64":
+        x = _off(words, off)
+        assert torch.equal(hv.sort_keys(x), torch.sort(words).values), what
+        return
+    k = _off(words.int(), off)
+    want, order = torch.sort(words.int(), stable=True)
+    if kind == "keys":
+        assert torch.equal(hv.sort(k), want), what
+    elif kind == "by_key":
+        ko, vo = hv.sort_by_key(k, idx)
+        assert torch.equal(ko, want) and torch.equal(vo, order), what
+    else:
+        v = _off(idx.int(), off)
+        ko, vo = hv.sort_pairs(k, v)
+        assert torch.equal(ko, want) and torch.equal(vo, order.int()), what
+
+
+def _sizes(kind):
+    return ((1 << 16, (1 << 16) + 5, 1 << 22) if kind in ("keys", "by_key")
+            else (1 << 22, (1 << 22) + 5))
+
+
+@pytest.mark.parametrize("off", (0, 1))
+@pytest.mark.parametrize("kind", KINDS)
+def test_one_pair_out_of_order(kind, off):
+    for n in _sizes(kind):
+        for rising in (True, False):
+            for p in EDGES + (n - 2,):
+                x = torch.arange(n, device=DEV) * 3
+                if not rising:
+                    x = x.flip(0).contiguous()
+                a, b = x[p].clone(), x[p + 1].clone()
+                x[p], x[p + 1] = b, a
+                what = (kind, n, off, rising, p)
+                print("first count", what, flush=True)
+                _check(kind, x, off, what)
+
+
+@pytest.mark.parametrize("off", (0, 1))
+@pytest.mark.parametrize("kind", KINDS)
+def test_lower_digits_constant(kind, off):
+    for n in _sizes(kind):
+        for shift in (8, 20, 32) if kind == "i64" else (8, 20):
+            g = torch.Generator(device=DEV).manual_seed(n + shift)
+            hi = 63 if kind == "i64" else 31
+            x = torch.randint(-(1 << (hi - shift)), 1 << (hi - shift), (n,), device=DEV,
+                              generator=g) << shift
+            what = (kind, n, off, shift)
+            print("constant digits", what, flush=True)
+            _check(kind, x, off, what)
+
+
+@pytest.mark.parametrize("kind,n", (("keys", 1 << 27), ("pairs", 1 << 26), ("i64", 1 << 26)))
+def test_largest_tiles(kind, n):
+    for p in (16383, n - 2):
+        x = torch.arange(n, device=DEV)
+        x[p], x[p + 1] = p + 1, p
+        print("first count", kind, n, p, flush=True)
+        _check(kind, x, 0, (kind, n, p))
