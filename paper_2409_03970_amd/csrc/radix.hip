@@ -1002,6 +1002,13 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
     // thread t < 256: where digit t's region of the output starts (FEW: this
     // tile's part of it)
     uint32_t region = 0;
+    // Keys alone may leave the first pass in any order within a digit: there
+    // an LDS atomic per key takes the place of the ballots (2^28 keys 3.18 ->
+    // 3.11 ms, 2^25 0.391 -> 0.374).  Lanes of one digit queue at its counter:
+    // with half the keys in one digit the sort took 3.10 against 2.90 ms, with a
+    // third of them it gained, so the line is at three eighths of the keys.
+    // A ragged tile is ranked in order, which puts its pads last.
+    __shared__ int spread;
     if constexpr (FEW) {
         // thread d + 256 h: digit d over every (NT / 256)th tile from tile h
         constexpr int H = NT / RADIX, U = 16;
@@ -1040,10 +1047,17 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
         const uint32_t ex = wave_inclusive(s) - s;
         *(uint4 *)&gpre[4 * lane] =
             make_uint4(ex, ex + t.x, ex + t.x + t.y, ex + t.x + t.y + t.z);
+        if constexpr (KIND == RADIX_KEYS) {
+            const uint32_t most = max(max(t.x, t.y), max(t.z, t.w));
+            const bool heavy = __builtin_amdgcn_ballot_w64(most > 3 * (uint32_t)(a.n >> 3)) != 0;
+            if (lane == 0)
+                spread = st.first && !heavy;
+        }
     }
     __syncthreads();
     if (tid < RADIX)
         region += gpre[tid];
+    const bool loose = KIND == RADIX_KEYS && __builtin_amdgcn_readfirstlane(spread) != 0;
 
     // Loads of a tile's words through buffer resources: they end at the
     // array's last element (zeros past it) and take one lane offset and
@@ -1103,27 +1117,44 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
         // ranks among the wave's keys of the same digit, two to a register
         *(uint2 *)&cnt[wave][4 * lane] = make_uint2(0, 0);
         uint32_t pos[K / 2];
+        if (loose && cnt_valid == T) {
+            // an LDS atomic per key, in no order among a row's lanes
+            uint32_t *c2 = (uint32_t *)cnt[wave];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const uint32_t d = (w[k] >> shift) & 255;
-            uint32_t mlo, mhi;
-            match_digit(d, mlo, mhi);
-            const uint32_t before =
-                __builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(mlo, 0));
-            const uint32_t all = __popc(mlo) + __popc(mhi);
-            const uint32_t c = cnt[wave][d];
-            if (k & 1)
-                pos[k / 2] |= (c + before) << 16;
-            else
-                pos[k / 2] = c + before;
-            if (before == 0)
-                cnt[wave][d] = (uint16_t)(c + all);
-            // the next row's reads follow this row's writes of other lanes:
-            // one wave's LDS operations complete in order, so only the
-            // compiler has to keep them so
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_sched_barrier(0);  // one row's masks at a time
+            for (int k = 0; k < K; ++k) {
+                const uint32_t d = (w[k] >> shift) & 255, sh = (d & 1) * 16;
+                const uint32_t c = (__hip_atomic_fetch_add(c2 + (d >> 1), 1u << sh, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_WAVEFRONT) >>
+                                    sh) &
+                                   0xffff;
+                if (k & 1)
+                    pos[k / 2] |= c << 16;
+                else
+                    pos[k / 2] = c;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const uint32_t d = (w[k] >> shift) & 255;
+                uint32_t mlo, mhi;
+                match_digit(d, mlo, mhi);
+                const uint32_t before =
+                    __builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(mlo, 0));
+                const uint32_t all = __popc(mlo) + __popc(mhi);
+                const uint32_t c = cnt[wave][d];
+                if (k & 1)
+                    pos[k / 2] |= (c + before) << 16;
+                else
+                    pos[k / 2] = c + before;
+                if (before == 0)
+                    cnt[wave][d] = (uint16_t)(c + all);
+                // the next row's reads follow this row's writes of other lanes:
+                // one wave's LDS operations complete in order, so only the
+                // compiler has to keep them so
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_sched_barrier(0);  // one row's masks at a time
+            }
         }
         if (tid < RADIX)
             gpre[tid] = first;

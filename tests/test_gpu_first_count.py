@@ -85,3 +85,16 @@ def test_largest_tiles(kind, n):
         x[p], x[p + 1] = p + 1, p
         print("first count", kind, n, p, flush=True)
         _check(kind, x, 0, (kind, n, p))
+
+
+@pytest.mark.parametrize("n", (1 << 16, 1 << 22, (1 << 22) + 5))
+def test_first_pass_ranks(n):
+    """Keys alone are ranked without order in the first pass: one digit for all
+    but a few keys, two, and the largest digit beside a ragged tile's pads."""
+    r = torch.arange(n, device=DEV)
+    for what, x in (("few", torch.where(r % 4099 == 0, r % 251, 7) | ((r % 3) << 8)),
+                    ("two", (r * 40503 >> 7) & 1 | ((r % 5) << 24)),
+                    ("top", 255 - (r % 2) | ((r * 7919 % 1000) << 8)),
+                    ("max", torch.where(r % 2 == 0, (1 << 31) - 1, r))):
+        print("first ranks", n, what, flush=True)
+        _check("keys", x, 0, (n, what))
