@@ -1316,14 +1316,17 @@ constexpr Shape SHAPES[] = {{256, 8}, {512, 16}, {512, 32}, {1024, 16}, {512, 8}
 // than the scan launch (2^16 keys 51 -> 42 us, 100,003 keys 53 -> 43; 64 tiles
 // of 2,048 keys 52 -> 50, 128 52 -> 64); keys alone large ones once
 // the runs go to HBM (2^26 keys 0.78 against 0.80 ms, 2^28 keys 3.78 against
-// 3.40).  Two words a key at K = 32 would spill.
+// 3.40).  Two words a key at K = 32 would spill; they take 16,384 with 1024
+// threads from 5 * 2^23 on (4e7 doubles 1.35 ms with either tile, 5e7 1.70 ->
+// 1.65, 5e7 pairs with random values 1.92 -> 1.80), keys with payloads from 2^25
+// (0.96 -> 0.88 ms; 3e7 zipf keys 0.557 against 0.583, 2^26 keys 2.14 -> 1.87).
 int shape_of(int kind, int64_t n)
 {
     if (n < ((int64_t)1 << 22))
         return n > ((int64_t)1 << 16) && n <= ((int64_t)1 << 17) ? 4 : 0;
     if (kind == RADIX_KEYS)
         return n >= ((int64_t)1 << 27) ? 2 : 1;
-    return kind != RADIX_BY_KEY && n >= ((int64_t)1 << 26) ? 3 : 1;
+    return n >= (int64_t)(kind == RADIX_BY_KEY ? 4 : 5) << 23 ? 3 : 1;
 }
 int tile_of(int kind, int64_t n)
 {
@@ -1522,7 +1525,8 @@ hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap
     case RADIX_BY_KEY:
         return shape == 0   ? run_radix<RADIX_BY_KEY, 0, 4, 4>(a, inplace, s)
                : shape == 4 ? run_radix<RADIX_BY_KEY, 4, 4, 2>(a, inplace, s)
-                          : run_radix<RADIX_BY_KEY, 1, 4, 2>(a, inplace, s);
+               : shape == 1 ? run_radix<RADIX_BY_KEY, 1, 4, 2>(a, inplace, s)
+                            : run_radix<RADIX_BY_KEY, 3, 4, 1>(a, inplace, s);
     }
     return hipErrorInvalidValue;
 }

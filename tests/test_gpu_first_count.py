@@ -78,13 +78,17 @@ def test_lower_digits_constant(kind, off):
             _check(kind, x, off, what)
 
 
-@pytest.mark.parametrize("kind,n", (("keys", 1 << 27), ("pairs", 1 << 26), ("i64", 1 << 26)))
+@pytest.mark.parametrize("kind,n", (("keys", 1 << 27), ("pairs", 5 << 23), ("i64", 5 << 23),
+                                    ("by_key", 1 << 25)))
 def test_largest_tiles(kind, n):
     for p in (16383, n - 2):
         x = torch.arange(n, device=DEV)
         x[p], x[p + 1] = p + 1, p
         print("first count", kind, n, p, flush=True)
         _check(kind, x, 0, (kind, n, p))
+    x = torch.arange(n + 5, device=DEV) * 40503 % 1000003 * 2039    # most keys out of order, a ragged last tile
+    _check(kind, x, 0, (kind, n, "shuffled"))
+    _check(kind, x, 1, (kind, n, "shuffled"))
 
 
 @pytest.mark.parametrize("n", (1 << 16, 1 << 22, (1 << 22) + 5))
