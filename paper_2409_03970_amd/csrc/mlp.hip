@@ -91,8 +91,13 @@ __device__ __forceinline__ float half_sum(float v)
 // 2.6 us.  Before, the per-sample factors of every gradient entry went
 // through memory (34 MB for 65,536 samples), one workgroup per 128 samples
 // multiplied them on the VALU, and five workgroups added 512 rows of partials
-// one after the other: 478 us a training step, now 15 us (12.7 here, 3.9 in the
+// one after the other: 478 us a training step, now 14 us (11.5 here, 3.9 in the
 // reduction; drawing the second block's samples during the first was no faster).
+// Apart from the matrix steps a launch's fixed part shows (1,024 samples: 10.5
+// us a step): the last sums over the lanes go through LDS, since DPP adds, a
+// dependent chain for each of 64 registers, cost 1 us more.  Eight waves of
+// half the blocks (the layers' vectors read again for each) take as long at
+// 65,536 samples, 12% less at 2^18 and a fifth more at 32,768 and below.
 //
 // TRAIN: the samples are a minibatch drawn here, position
 // i_k = SplitMix64(seed, step * 2^32 + k) mod m of the sorted sample, x its
@@ -194,19 +199,30 @@ __global__ __launch_bounds__(256, 1) void cdf_grad_kernel(
         __builtin_amdgcn_wave_barrier();
     }
 
+    // The lanes' sums of the four vectors, turned like the operands above:
+    // then half g of the wave adds up vector g, a unit to a lane.
+    const auto column_sums = [&](const float(&v0)[16], const float(&v1)[16], int at) {
+        float *t = turn[wave][0];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int u = unit(r, g);
-        const float a1 = half_sum(gw1[r]), a2 = half_sum(gb1[r]);
-        const float a3 = half_sum(gb2[r]), a4 = half_sum(gw3[r]);
-        if (s == 31) {
-            sums[wave][u] = a1;
-            sums[wave][H + u] = a2;
-            sums[wave][2 * H + H * H + u] = a3;
-            sums[wave][3 * H + H * H + u] = a4;
+        for (int r = 0; r < 16; ++r) {
+            t[s * LD + unit(r, g)] = v0[r];
+            t[H * LD + s * LD + unit(r, g)] = v1[r];
         }
-        sums[wave][2 * H + u * H + s] = gw2[r];
-    }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        float q[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int i = 0; i < H; ++i)
+            q[i & 3] += t[(g * H + i) * LD + s];
+        sums[wave][at + lane] = (q[0] + q[1]) + (q[2] + q[3]);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    column_sums(gw1, gb1, 0);
+    column_sums(gb2, gw3, 2 * H + H * H);
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        sums[wave][2 * H + unit(r, g) * H + s] = gw2[r];
     gb3 = half_sum(gb3);
     loss = half_sum(loss);
     if (lane == 31) {
