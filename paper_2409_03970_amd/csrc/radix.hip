@@ -939,13 +939,18 @@ __device__ __forceinline__ void copy_step(const RadixArgs &a, const Step &st)
     }
 }
 
-//
-// FEW (one workgroup to a tile, at most FEW_TILES tiles): no scan launch.
-// Every workgroup adds up the tiles' counts itself, and in the first pass
-// makes the plan.
-template <int NT, int K, int KIND, int WAVES, bool FEW>
+// Where a scatter's output positions come from.  OF_SCAN: the scan launch.
+// OF_TILES (one workgroup to a tile, at most FEW_TILES tiles): every workgroup
+// adds up the tiles' counts itself, and in the first pass makes the plan.
+// OF_CHUNKS: the chunks' counts likewise, 512 KB for a workgroup, more than the
+// scan launch costs; the second round's passes do so, which hardly ever run,
+// since a launch that returns at once still takes 1.5 us (2^24 pairs with index
+// values 352 -> 341 us, 2^26 1197 -> 1184).
+enum { OF_SCAN = 0, OF_TILES = 1, OF_CHUNKS = 2 };
+template <int NT, int K, int KIND, int WAVES, int SUMS>
 __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass, int inplace)
 {
+    constexpr bool FEW = SUMS == OF_TILES;
     constexpr int T = NT * K;
     constexpr int NW = NT / 64;
     constexpr int B = 8;  // positions written out at a time
@@ -1009,22 +1014,24 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
     // third of them it gained, so the line is at three eighths of the keys.
     // A ragged tile is ranked in order, which puts its pads last.
     __shared__ int spread;
-    if constexpr (FEW) {
-        // thread d + 256 h: digit d over every (NT / 256)th tile from tile h
+    int chunk = FEW ? (int)tile : (int)(tile >> a.per_log2);  // the last one region counts to
+    if constexpr (SUMS != OF_SCAN) {
+        // thread d + 256 h: digit d over every (NT / 256)th tile (or chunk) from h
         constexpr int H = NT / RADIX, U = 16;
+        const int rows = FEW ? (int)a.tiles : a.chunks;
         uint32_t *sums = xch;  // [h][digit]: all tiles', then the ones before
         uint32_t all = 0, mine = 0;
-        for (int c0 = tid / RADIX; c0 < (int)a.tiles; c0 += U * H) {
+        for (int c0 = tid / RADIX; c0 < rows; c0 += U * H) {
             uint32_t v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                v[u] = c0 + u * H < (int)a.tiles
+                v[u] = c0 + u * H < rows
                            ? a.counts[(c0 + u * H) * RADIX + (tid & (RADIX - 1))]
                            : 0;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 all += v[u];
-                mine += c0 + u * H < (int)tile ? v[u] : 0;
+                mine += c0 + u * H < chunk ? v[u] : 0;
             }
         }
         sums[tid] = all;
@@ -1042,7 +1049,7 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
         __syncthreads();
     }
     if (wave == 0) {
-        const uint4 t = *(const uint4 *)((FEW ? gbase : a.totals) + 4 * lane);
+        const uint4 t = *(const uint4 *)((SUMS != OF_SCAN ? gbase : a.totals) + 4 * lane);
         const uint32_t s = t.x + t.y + t.z + t.w;
         const uint32_t ex = wave_inclusive(s) - s;
         *(uint4 *)&gpre[4 * lane] =
@@ -1083,8 +1090,15 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
     for (; tile < tile1; tile += slots) {
         const int64_t base = tile * T;
         const int cnt_valid = a.n - base < T ? (int)(a.n - base) : T;
+        if constexpr (SUMS == OF_CHUNKS) {
+            for (; chunk < (int)(tile >> a.per_log2); ++chunk)
+                if (tid < RADIX)
+                    region += a.counts[chunk * RADIX + tid];
+        }
         uint32_t first = region;
-        if (!FEW && tid < RADIX)
+        if (SUMS == OF_CHUNKS && tid < RADIX)
+            first += a.rows[tile * RADIX + tid];
+        if (SUMS == OF_SCAN && tid < RADIX)
             first += a.rows[tile * RADIX + tid] + a.counts[(tile >> a.per_log2) * RADIX + tid];
         int t0 = tid;
         asm("" : "+v"(t0));  // keeps the row offsets out of registers held across tiles
@@ -1123,10 +1137,9 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const uint32_t d = (w[k] >> shift) & 255, sh = (d & 1) * 16;
-                const uint32_t c = (__hip_atomic_fetch_add(c2 + (d >> 1), 1u << sh, __ATOMIC_RELAXED,
-                                                           __HIP_MEMORY_SCOPE_WAVEFRONT) >>
-                                    sh) &
-                                   0xffff;
+                const uint32_t two = __hip_atomic_fetch_add(
+                    c2 + (d >> 1), 1u << sh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                const uint32_t c = (two >> sh) & 0xffff;
                 if (k & 1)
                     pos[k / 2] |= c << 16;
                 else
@@ -1419,8 +1432,8 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
                     hipLaunchKernelGGL((radix_count_first<KIND, T>), grid, dim3(COUNT_NT), 0, s, a);
                 else
                     hipLaunchKernelGGL((radix_count<KIND, T>), grid, dim3(COUNT_NT), 0, s, a, p);
-                hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, true>), grid, dim3(NT), 0, s,
-                                   a, p, (int)inplace);
+                hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, OF_TILES>), grid, dim3(NT),
+                                   0, s, a, p, (int)inplace);
             }
             return hipGetLastError();
         }
@@ -1448,8 +1461,8 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
             hipLaunchKernelGGL((radix_count<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a, p);
         hipLaunchKernelGGL(radix_scan, dim3(RADIX / 16 + (p == 0)), dim3(512), 0, s, a, p, passes,
                            (int)two, (int)keys64, (int)inplace);
-        hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, false>), sgrid, dim3(NT), 0, s, a, p,
-                           (int)inplace);
+        hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, OF_SCAN>), sgrid, dim3(NT), 0, s, a,
+                           p, (int)inplace);
     }
     if constexpr (two) {
         if (a.sample) {
@@ -1461,10 +1474,8 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
             a.v[B_IN] = a.v[B_OUT];
             for (int p = 0; p < passes; ++p) {
                 hipLaunchKernelGGL((radix_count<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a, p);
-                hipLaunchKernelGGL(radix_scan, dim3(RADIX / 16), dim3(512), 0, s, a, p, passes,
-                                   (int)two, (int)keys64, 1);
-                hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, false>), sgrid, dim3(NT), 0,
-                                   s, a, p, 1);
+                hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, OF_CHUNKS>), sgrid, dim3(NT),
+                                   0, s, a, p, 1);
             }
         }
     }

@@ -3,6 +3,7 @@ array: a single pair of elements out of order at the edges of a lane's load, a
 wave, a tile and the array must not pass for presorted input, and passes whose
 lower digits are constant count the caller's words, on and off the 16-byte
 grid, with and without a ragged last tile."""
+import numpy as np
 import pytest
 import torch
 
@@ -86,7 +87,8 @@ def test_largest_tiles(kind, n):
         x[p], x[p + 1] = p + 1, p
         print("first count", kind, n, p, flush=True)
         _check(kind, x, 0, (kind, n, p))
-    x = torch.arange(n + 5, device=DEV) * 40503 % 1000003 * 2039    # most keys out of order, a ragged last tile
+    # most keys out of order, a ragged last tile
+    x = torch.arange(n + 5, device=DEV) * 40503 % 1000003 * 2039
     _check(kind, x, 0, (kind, n, "shuffled"))
     _check(kind, x, 1, (kind, n, "shuffled"))
 
@@ -102,3 +104,30 @@ def test_first_pass_ranks(n):
                     ("max", torch.where(r % 2 == 0, (1 << 31) - 1, r))):
         print("first ranks", n, what, flush=True)
         _check("keys", x, 0, (n, what))
+
+
+@pytest.mark.parametrize("kind", ("i64", "pairs"))
+def test_second_round_with_the_largest_tile(kind):
+    """A group too long for the finish, planted where the sample of 2^19
+    elements (element j at SplitMix64(j) * n / 2^64) does not look."""
+    n = (5 << 23) + 4097
+    print("second round", kind, n, flush=True)
+    with np.errstate(over="ignore"):
+        z = (np.arange(1 << 19, dtype=np.uint64) + np.uint64(1)) * np.uint64(0x9E3779B97F4A7C15)
+        z = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+        z = (z ^ (z >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+        z ^= z >> np.uint64(31)
+        lo = ((z & np.uint64(0xffffffff)) * np.uint64(n)) >> np.uint64(32)
+        seen = ((z >> np.uint64(32)) * np.uint64(n) + lo) >> np.uint64(32)
+    rng = np.random.default_rng(9)
+    at = np.setdiff1d(rng.integers(0, n, 40000), seen.astype(np.int64))
+    x = rng.integers(-2**63, 2**63, n, dtype=np.int64)
+    x[at] = (77 << 40) + rng.integers(0, 2**32, len(at))
+    x = torch.from_numpy(x).to(DEV)
+    want = torch.sort(x).values
+    if kind == "i64":
+        got = hv.sort_keys(x)
+    else:
+        ko, vo = hv.sort_pairs((x >> 32).int(), ((x & 0xffffffff) - 2**31).int())
+        got = (ko.long() << 32) | (vo.long() + 2**31)
+    assert torch.equal(got, want)
