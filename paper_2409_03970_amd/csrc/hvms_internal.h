@@ -70,8 +70,7 @@ struct RadixArgs {
     uint32_t *totals;       // [digit]
     uint32_t *counts;       // [chunk][digit]
     uint32_t *rows;         // [tile][digit]: keys of the chunk's tiles before
-    uint64_t *sample;       // null: no sample is taken
-    uint32_t *sample_pairs; // [run][digit]
+    uint32_t *sample_pairs; // [run][digit]; null: no sample is taken
     longlong2 *groups;      // first element and length
     int chunks;
     int sample_runs;
@@ -86,7 +85,7 @@ struct RadixIO {
     uint64_t *pout;
 };
 struct RadixLayout {
-    int64_t a_k, a_v, b_k, b_v, a_p, ctl, totals, info, counts, rows, sample, sample_pairs,
+    int64_t a_k, a_v, b_k, b_v, a_p, ctl, totals, info, counts, rows, sample_pairs,
         groups, total;
 };
 RadixLayout radix_layout(int kind, int64_t n);

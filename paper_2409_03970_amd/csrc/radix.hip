@@ -98,6 +98,14 @@ enum { NOT_ASCENDING = 1, NOT_DESCENDING = 2, VALUES_NOT_ASCENDING = 4 };
 struct ChunkInfo {
     uint32_t and0, or0, and1, or1, flags, pad[3];
 };
+// Whether the plan asks how many low digits can be left out: not for presorted
+// input, and not for pairs that skip their value digits (the keys' four are
+// too few to leave out two of them from SAMPLE_MIN elements on).
+__device__ __forceinline__ bool sample_matters(uint32_t flags, bool keys64)
+{
+    return (flags & NOT_ASCENDING) && (flags & NOT_DESCENDING) &&
+           (keys64 || (flags & VALUES_NOT_ASCENDING));
+}
 
 __device__ __forceinline__ uint32_t map_key(uint32_t v, RadixMap m)
 {
@@ -560,7 +568,7 @@ __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64,
         part[threadIdx.x / 64] = f;
     if (threadIdx.x < 8) {  // sampled pairs that first differ in digit threadIdx.x
         uint32_t c = 0;
-        if (a.sample)
+        if (a.sample_pairs)
             for (int r = 0; r < a.sample_runs; ++r)
                 c += a.sample_pairs[r * 8 + threadIdx.x];
         same[threadIdx.x] = c;
@@ -600,7 +608,7 @@ __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64,
         }
         if (two && !keys64 && !(f.flags & VALUES_NOT_ASCENDING))
             need &= 0xf0;
-        if (a.sample) {
+        if (a.sample_pairs && sample_matters(f.flags, keys64)) {
             // The most low digits without which the sample leaves an element
             // alike with at most a quarter of another one on average.  m
             // elements in groups of g are m g / n of that, so groups of more
@@ -675,7 +683,7 @@ __global__ __launch_bounds__(512) void radix_scan(RadixArgs a, int pass, int pas
 // Elements of two words rarely need all their eight digits: once the top ones
 // tell nearly all of them apart, the few that are left alike stand next to
 // each other and are ordered where they are.  How many digits that takes is
-// estimated from a sample sorted in runs by the block sort:
+// estimated from a sample sorted in runs:
 // neighbours that are equal in the top digits and different below are what a
 // shorter key would leave alike.  The finish checks its own work, so the
 // estimate only costs time where it is wrong: the second round then makes
@@ -686,32 +694,60 @@ __global__ __launch_bounds__(512) void radix_scan(RadixArgs a, int pass, int pas
 // Sample element j comes from position SplitMix64(j) * n / 2^64.  (From the
 // j-th of equal parts of the input it would not do: in presorted input the
 // elements that are alike stand side by side and would never meet.)
-template <int KIND> __global__ __launch_bounds__(256) void radix_sample(RadixArgs a)
+//
+// A workgroup draws a run, sorts it and counts its neighbours by the highest
+// digit in which they differ (equal neighbours are no pair to be told apart).
+// It runs after the first count, whose flags say whether the plan will ask:
+// 2^24 pairs with index values 341 -> 304 us, 2^26 1184 -> 1130.  Drawn by a
+// launch over the whole chip, sorted by the block sort and counted by a third
+// launch, it took 15 us more for 5e7 doubles, 6 us less for 2^24 pairs with
+// random values.
+template <int KIND> __global__ __launch_bounds__(SAMPLE_LEN / 8) void radix_sample(RadixArgs a)
 {
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    uint64_t z = ((uint64_t)j + 1) * 0x9E3779B97F4A7C15ull;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    const int64_t i = (int64_t)__umul64hi(z ^ (z >> 31), (uint64_t)a.n);
-    const Elem e = map_elem2<KIND>(load_raw<KIND>(a, B_IN, i), a);
-    // signed order, as the block sort compares
-    a.sample[j] = ((uint64_t)(e.hi ^ 0x80000000u) << 32) | e.lo;
-}
-
-// Neighbours of sorted run blockIdx.x by the highest digit in which they
-// differ (equal neighbours are no pair to be told apart).
-__global__ __launch_bounds__(256) void radix_sample_pairs(RadixArgs a)
-{
-    __shared__ uint32_t c[8];
+    constexpr int R = 8, NT = SAMPLE_LEN / R;
+    __shared__ __attribute__((aligned(16))) int64_t S[LdsSkew<int64_t>::size(R * NT)];
+    __shared__ uint32_t c[8], flags;
+    const LdsSkew<int64_t> Z{S, 0};
     if (threadIdx.x < 8)
         c[threadIdx.x] = 0;
+    if (threadIdx.x == 8)
+        flags = 0;
     __syncthreads();
-    const uint64_t *x = a.sample + (int64_t)blockIdx.x * SAMPLE_LEN;
-    for (int i = threadIdx.x; i + 1 < SAMPLE_LEN; i += 256) {
-        const uint64_t d = x[i] ^ x[i + 1];
-        if (d)
-            atomicAdd(&c[(63 - __clzll((long long)d)) >> 3], 1u);
+    uint32_t f = 0;
+    for (int i = threadIdx.x; i < a.chunks; i += NT)
+        f |= ((const ChunkInfo *)a.info)[i].flags;
+    if (f)
+        atomicOr(&flags, f);
+    __syncthreads();
+    if (!sample_matters(flags, KIND == RADIX_KEYS64))
+        return;
+    int64_t v[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        uint64_t z = ((uint64_t)blockIdx.x * SAMPLE_LEN + NT * j + threadIdx.x + 1) *
+                     0x9E3779B97F4A7C15ull;
+        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+        const int64_t i = (int64_t)__umul64hi(z ^ (z >> 31), (uint64_t)a.n);
+        const Elem e = map_elem2<KIND>(load_raw<KIND>(a, B_IN, i), a);
+        // signed order, as the block sort compares
+        v[j] = (int64_t)(((uint64_t)(e.hi ^ 0x80000000u) << 32) | e.lo);
     }
+    sort_tile_core<R, NT, int64_t, 0>(S, v, threadIdx.x, 6, 4);
+    uint32_t count[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int i = threadIdx.x + NT * j;
+        const uint64_t d = i + 1 < SAMPLE_LEN ? (uint64_t)(Z[i] ^ Z[i + 1]) : 0;
+        const int t = d ? (63 - __clzll((long long)d)) >> 3 : 8;
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            count[q] += __popcll(__builtin_amdgcn_ballot_w64(t == q));
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        if (lane_id() == q)
+            atomicAdd(&c[q], count[q]);
     __syncthreads();
     if (threadIdx.x < 8)
         a.sample_pairs[blockIdx.x * 8 + threadIdx.x] = c[threadIdx.x];
@@ -1402,8 +1438,6 @@ RadixLayout radix_layout(int kind, int64_t n)
     w.rows = off;
     off += align256(tiles * RADIX * 4);
     if ((kind == RADIX_PAIRS || kind == RADIX_KEYS64) && n >= SAMPLE_MIN) {
-        w.sample = off;
-        off += (int64_t)sample_runs(n) * SAMPLE_LEN * 8;
         w.sample_pairs = off;
         off += sample_runs(n) * 8 * 4;
         w.groups = off;
@@ -1442,30 +1476,23 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
     int64_t wg = a.tiles < fit ? a.tiles : fit;
     wg = (wg + 7) & ~(int64_t)7;
     const dim3 cgrid((unsigned)a.chunks), sgrid((unsigned)wg);
-    if (a.sample) {
-        const int64_t samples = (int64_t)a.sample_runs * SAMPLE_LEN;
-        hipLaunchKernelGGL(radix_sample<KIND>, dim3((unsigned)(samples / 256)), dim3(256), 0, s, a);
-        KeyMap packed;
-        packed.packed = true;
-        const hipError_t e = launch_block_sort(8, 1024, true, (const int32_t *)a.sample, nullptr,
-                                               (int32_t *)a.sample, nullptr, samples, 6, 4, false,
-                                               s, 0, packed, packed);
-        if (e != hipSuccess)
-            return e;
-        hipLaunchKernelGGL(radix_sample_pairs, dim3(a.sample_runs), dim3(256), 0, s, a);
-    }
     for (int p = 0; p < passes; ++p) {
         if (p == 0)
             hipLaunchKernelGGL((radix_count_first<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a);
         else
             hipLaunchKernelGGL((radix_count<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a, p);
+        if constexpr (two) {
+            if (p == 0 && a.sample_pairs)
+                hipLaunchKernelGGL(radix_sample<KIND>, dim3(a.sample_runs), dim3(SAMPLE_LEN / 8), 0,
+                                   s, a);
+        }
         hipLaunchKernelGGL(radix_scan, dim3(RADIX / 16 + (p == 0)), dim3(512), 0, s, a, p, passes,
                            (int)two, (int)keys64, (int)inplace);
         hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, OF_SCAN>), sgrid, dim3(NT), 0, s, a,
                            p, (int)inplace);
     }
     if constexpr (two) {
-        if (a.sample) {
+        if (a.sample_pairs) {
             hipLaunchKernelGGL(radix_finish<KIND>, dim3((unsigned)((a.n + 2047) / 2048)),
                                dim3(256), 0, s, a);
             hipLaunchKernelGGL(radix_groups<KIND>, dim3(2 * device_cus()), dim3(1024), 0, s, a);
@@ -1505,8 +1532,7 @@ hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap
     a.info = base + w.info;
     a.counts = (uint32_t *)(base + w.counts);
     a.rows = (uint32_t *)(base + w.rows);
-    if (w.sample) {
-        a.sample = (uint64_t *)(base + w.sample);
+    if (w.sample_pairs) {
         a.sample_runs = sample_runs(n);
         a.sample_pairs = (uint32_t *)(base + w.sample_pairs);
         a.groups = (longlong2 *)(base + w.groups);
