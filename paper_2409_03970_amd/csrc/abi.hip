@@ -145,8 +145,8 @@ bool library_choice(const hvms_options *o)
 // Sizes that take the digit passes (radix.hip) where the choice is the
 // library's.  Keys alone and the sort by key: past 2^15 keys, where the merge
 // sort takes its third merge level (2^15 uniform keys 38 against 37 us, 2^16 42
-// against 50, 2^20 64 against 109, 2^28 3.2 against 5.7 ms).  Two-word elements
-// make up to eight passes: from 2^22 (pairs of any order there 0.21 against
+// against 50, 2^20 62 against 108, 2^28 3.1 against 5.7 ms).  Two-word elements
+// make up to eight passes: from 2^22 (pairs of any order there 0.11-0.21 against
 // 0.25-0.31 ms; at 2^21 presorted keys are even).
 constexpr int64_t kRadixMin = (1 << 15) + 1, kRadixMin2 = 1 << 22;
 constexpr int64_t kRadixMax = ((int64_t)1 << 32) - (1 << 16);  // 32-bit positions

@@ -23,7 +23,7 @@
 //
 // What bounds a pass (2^28 uniform keys): the count reads 1.07 GB in 0.20 ms
 // (5.5 TB/s; 0.27 with loads that fill the memory-side cache on their way).
-// The scatter takes 0.61 ms for
+// The scatter takes 0.61 ms (0.58 in the first pass, see `spread`) for
 // 2.15 GB: with its ranks left out and its writes made linear it would take
 // 0.39, with the writes alone linear 0.52, so both the partial cache lines at
 // the ends of the runs and the 55 VALU operations per key (32 of them the
@@ -688,8 +688,8 @@ __global__ __launch_bounds__(512) void radix_scan(RadixArgs a, int pass, int pas
 // shorter key would leave alike.  The finish checks its own work, so the
 // estimate only costs time where it is wrong: the second round then makes
 // every pass that is needed.  Pairs of 2^26 uniform keys and random values take
-// four passes and the finish, 1.85 ms, for eight passes 2.78 and the merge sort
-// 2.62; 2^26 doubles five and 2.2 ms for 2.79 and 2.72.
+// four passes and the finish, 1.80 ms, for eight passes 2.48 and the merge sort
+// 2.62; 5e7 doubles five and 1.61 ms for 2.19 by the merge sort.
 
 // Sample element j comes from position SplitMix64(j) * n / 2^64.  (From the
 // j-th of equal parts of the input it would not do: in presorted input the
