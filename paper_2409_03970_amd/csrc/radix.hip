@@ -610,14 +610,20 @@ __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64,
             need &= 0xf0;
         if (a.sample_pairs && sample_matters(f.flags, keys64)) {
             // The most low digits without which the sample leaves an element
-            // alike with at most a quarter of another one on average.  m
-            // elements in groups of g are m g / n of that, so groups of more
-            // than GROUP_MAX elements slip through only where there are few.
+            // alike with at most half another one on average, a quarter from
+            // 2^27 elements on.  m elements in groups of g are m g / n of that,
+            // so groups of more than GROUP_MAX elements slip through only
+            // where there are few, and groups that fill the list (longer than
+            // half a window) are GROUPS_MAX * 33^2 / n of it or more.  Pairs of
+            // mixture keys and random values, between the two: 2^26 2.83 ms
+            // with all eight passes, 2.46 with six; 2^27 5.75 and 5.95, where
+            // 9,232 groups were listed.
             const double pairs = 0.5 * a.sample_runs * SAMPLE_LEN * SAMPLE_LEN;
+            const double most = fmax(0.25, 0.5 * fmin(1.0, 67108864.0 / (double)a.n));
             uint32_t alike = 0, drop = 0;
             for (int d = 1; d < 8; ++d) {
                 alike += same[d - 1];
-                if ((double)alike * (double)a.n <= 0.25 * pairs)
+                if ((double)alike * (double)a.n <= most * pairs)
                     drop = d;
             }
             const uint32_t low = need & ((1u << drop) - 1);
