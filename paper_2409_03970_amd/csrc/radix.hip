@@ -47,6 +47,7 @@
 // Skipped launches return at once; nothing is read back by the host.
 #include "common.h"
 #include "hvms_internal.h"
+#include "radix_plan.h"
 
 namespace hvms {
 
@@ -56,24 +57,9 @@ constexpr int RADIX = 256;
 constexpr int COUNT_NT = 512;
 constexpr int MAX_CHUNKS = 512;
 constexpr int FEW_TILES = 32;
-constexpr int SAMPLE_LEN = 8192, SAMPLE_RUNS_MAX = 64;
+constexpr int SAMPLE_RUNS_MAX = 64;
 constexpr int64_t SAMPLE_MIN = (int64_t)1 << 24;  // elements from which a sample is taken
 constexpr int COPIES = 8;  // interleaved histogram copies of the count kernel
-
-// buffers of a sort; the steps alternate between them
-enum { B_IN = 0, B_A = 1, B_B = 2, B_OUT = 3 };
-enum { STEP_SKIP = 0, STEP_SCATTER = 1, STEP_COPY = 2, STEP_REVERSE = 3 };
-
-struct Step {
-    uint32_t mode, src, dst, first, last;
-};
-
-struct Ctl {
-    Step step[2][8];  // of the first round and of the second (see radix_finish)
-    uint32_t drop;    // low digits the first round left out and radix_finish orders
-    uint32_t groups;  // groups listed by radix_finish
-    uint32_t again;   // set: these could not order them, the second round sorts
-};
 
 // The step of a pass, in scalar registers.
 __device__ __forceinline__ Step step_of(const Ctl *ctl, int round, int pass)
@@ -93,19 +79,10 @@ __device__ __forceinline__ Step step_of(const RadixArgs &a, int pass)
     return step_of((const Ctl *)a.ctl, a.round, pass);
 }
 
-// What one chunk's count says about the input's order (flag set = not so).
-enum { NOT_ASCENDING = 1, NOT_DESCENDING = 2, VALUES_NOT_ASCENDING = 4 };
+// What one chunk's count found; flags as of the plan.
 struct ChunkInfo {
     uint32_t and0, or0, and1, or1, flags, pad[3];
 };
-// Whether the plan asks how many low digits can be left out: not for presorted
-// input, and not for pairs that skip their value digits (the keys' four are
-// too few to leave out two of them from SAMPLE_MIN elements on).
-__device__ __forceinline__ bool sample_matters(uint32_t flags, bool keys64)
-{
-    return (flags & NOT_ASCENDING) && (flags & NOT_DESCENDING) &&
-           (keys64 || (flags & VALUES_NOT_ASCENDING));
-}
 
 __device__ __forceinline__ uint32_t map_key(uint32_t v, RadixMap m)
 {
@@ -498,50 +475,6 @@ __device__ __forceinline__ uint32_t wave_inclusive(uint32_t x)
     return x;
 }
 
-// The steps of one round: modes by pass, and the buffers they go through.
-__device__ void set_steps(Step *step, const uint32_t *mode, int passes, bool keys64)
-{
-    int steps = 0, j = 0;
-    for (int p = 0; p < passes; ++p)
-        steps += mode[p] != STEP_SKIP;
-    uint32_t cur = B_IN;
-    for (int p = 0; p < passes; ++p) {
-        Step s{mode[p], 0, 0, 0, 0};
-        if (mode[p] != STEP_SKIP) {
-            s.first = j == 0;
-            s.last = j == steps - 1;
-            s.src = cur;
-            if (s.last)
-                s.dst = B_OUT;
-            else if (keys64)
-                s.dst = (j & 1) ? B_B : B_A;
-            else
-                s.dst = ((steps - 1 - j) & 1) ? B_A : B_OUT;
-            cur = s.dst;
-            ++j;
-        }
-        step[p] = s;
-    }
-}
-
-// Passes over the digits in `need`.  In place, the first step must not write
-// the array it reads: where the count of steps would make it, a pass that is
-// not needed copies instead.
-__device__ void scatter_modes(uint32_t *mode, uint32_t need, int passes, bool keys64, bool inplace)
-{
-    int steps = 0;
-    for (int p = 0; p < passes; ++p) {
-        mode[p] = (need >> p) & 1 ? STEP_SCATTER : STEP_SKIP;
-        steps += (int)((need >> p) & 1);
-    }
-    if (inplace && (keys64 ? steps == 1 : (steps & 1) != 0))
-        for (int p = 0; p < passes; ++p)
-            if (mode[p] == STEP_SKIP) {
-                mode[p] = STEP_COPY;
-                break;
-            }
-}
-
 // The steps of the sort from what the chunks found, by one workgroup of at
 // most 512 threads (ctl: where they go, in LDS or memory).
 __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64, bool inplace,
@@ -583,60 +516,9 @@ __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64,
         f.or1 |= part[w].or1;
         f.flags |= part[w].flags;
     }
-    uint32_t mode[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    const bool ascending = !(f.flags & NOT_ASCENDING);
-    const bool descending = !(f.flags & NOT_DESCENDING);
-    ctl->drop = 0;
-    ctl->groups = 0;
-    ctl->again = 0;
-    if (ascending) {
-        mode[passes - 1] = STEP_COPY;
-    } else if (descending) {
-        mode[passes - 1] = STEP_REVERSE;
-        if (inplace) {  // through the scratch, since both ends move
-            mode[passes - 2] = STEP_REVERSE;
-            mode[passes - 1] = STEP_COPY;
-        }
-    } else {
-        // a set bit: this bit differs between two elements
-        const uint32_t var0 = f.and0 ^ f.or0, var1 = f.and1 ^ f.or1;
-        uint32_t need = 0;
-        for (int p = 0; p < passes; ++p) {
-            const uint32_t var = (two && p < 4) ? var0 : var1;
-            if ((var >> (8 * (p & 3))) & 255)
-                need |= 1u << p;
-        }
-        if (two && !keys64 && !(f.flags & VALUES_NOT_ASCENDING))
-            need &= 0xf0;
-        if (a.sample_pairs && sample_matters(f.flags, keys64)) {
-            // The most low digits without which the sample leaves an element
-            // alike with at most half another one on average, a quarter from
-            // 2^27 elements on.  m elements in groups of g are m g / n of that,
-            // so groups of more than GROUP_MAX elements slip through only
-            // where there are few, and groups that fill the list (longer than
-            // half a window) are GROUPS_MAX * 33^2 / n of it or more.  Pairs of
-            // mixture keys and random values, between the two: 2^26 2.83 ms
-            // with all eight passes, 2.46 with six; 2^27 5.75 and 5.95, where
-            // 9,232 groups were listed.
-            const double pairs = 0.5 * a.sample_runs * SAMPLE_LEN * SAMPLE_LEN;
-            const double most = fmax(0.25, 0.5 * fmin(1.0, 67108864.0 / (double)a.n));
-            uint32_t alike = 0, drop = 0;
-            for (int d = 1; d < 8; ++d) {
-                alike += same[d - 1];
-                if ((double)alike * (double)a.n <= most * pairs)
-                    drop = d;
-            }
-            const uint32_t low = need & ((1u << drop) - 1);
-            if (__popc(low) >= 2) {
-                scatter_modes(mode, need, passes, keys64, true);
-                set_steps(ctl->step[1], mode, passes, keys64);
-                ctl->drop = drop;
-                need &= ~low;
-            }
-        }
-        scatter_modes(mode, need, passes, keys64, inplace);
-    }
-    set_steps(ctl->step[0], mode, passes, keys64);
+    plan_sort(Found{f.flags, f.and0 ^ f.or0, f.and1 ^ f.or1, same,
+                    a.sample_pairs ? a.sample_runs : 0, a.n},
+              passes, two, keys64, inplace, ctl);
 }
 
 // Workgroup g: the exclusive prefixes of the counts of digits 16 g .. 16 g +
