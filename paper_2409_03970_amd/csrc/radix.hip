@@ -80,9 +80,12 @@ __device__ __forceinline__ Step step_of(const RadixArgs &a, int pass)
 }
 
 // What one chunk's count found; flags as of the plan.
+// near0, near1: the smallest difference (xor, minus 1) between an element and the
+// one after it, over those that differ in the low word only, and in the high word.
 struct ChunkInfo {
-    uint32_t and0, or0, and1, or1, flags, pad[3];
+    uint32_t and0, or0, and1, or1, flags, near0, near1, pad;
 };
+constexpr ChunkInfo NOTHING_FOUND{~0u, 0u, ~0u, 0u, 0u, ~0u, ~0u, 0u};
 
 __device__ __forceinline__ uint32_t map_key(uint32_t v, RadixMap m)
 {
@@ -179,6 +182,35 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t x)
     return x;
 }
 
+__device__ __forceinline__ uint32_t wave_min(uint32_t x)
+{
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2)
+        x = min(x, (uint32_t)__shfl_xor((int)x, d));
+    return x;
+}
+__device__ __forceinline__ ChunkInfo wave_info(ChunkInfo f)
+{
+    f.and0 = wave_and(f.and0);
+    f.or0 = wave_or(f.or0);
+    f.and1 = wave_and(f.and1);
+    f.or1 = wave_or(f.or1);
+    f.flags = wave_or(f.flags);
+    f.near0 = wave_min(f.near0);
+    f.near1 = wave_min(f.near1);
+    return f;
+}
+__device__ __forceinline__ void add_info(ChunkInfo &f, const ChunkInfo &g)
+{
+    f.and0 &= g.and0;
+    f.or0 |= g.or0;
+    f.and1 &= g.and1;
+    f.or1 |= g.or1;
+    f.flags |= g.flags;
+    f.near0 = min(f.near0, g.near0);
+    f.near1 = min(f.near1, g.near1);
+}
+
 // Digit d of the workgroup's histogram so far (d < 256).
 __device__ __forceinline__ uint32_t hist_sum(const uint32_t *hist, int d)
 {
@@ -252,9 +284,14 @@ __device__ __forceinline__ void count_first_tile(const RadixArgs &a, int64_t i0,
                 // a stable sort may reverse only where no two keys are equal
                 bool l = KIND == RADIX_BY_KEY ? k[j].hi <= k[j + 1].hi : k[j].hi < k[j + 1].hi;
                 if constexpr (TWO) {
+                    // (one compare each: by words the flags are kept in vector registers)
+                    const uint64_t x = (uint64_t)k[j].hi << 32 | k[j].lo;
+                    const uint64_t y = (uint64_t)k[j + 1].hi << 32 | k[j + 1].lo;
+                    g = x > y;
+                    l = x < y;
                     const bool eq = k[j].hi == k[j + 1].hi;
-                    g = g || (eq && k[j].lo > k[j + 1].lo);
-                    l = l || (eq && k[j].lo < k[j + 1].lo);
+                    f.near0 = min(f.near0, eq ? (k[j].lo ^ k[j + 1].lo) - 1 : ~0u);
+                    f.near1 = min(f.near1, (k[j].hi ^ k[j + 1].hi) - 1);
                     if constexpr (KIND == RADIX_PAIRS)
                         vgt = vgt || k[j].lo > k[j + 1].lo;
                     f.and0 &= k[j].lo;
@@ -282,7 +319,7 @@ __global__ __launch_bounds__(COUNT_NT) void radix_count_first(RadixArgs a)
     for (int i = threadIdx.x; i < RADIX * COPIES; i += COUNT_NT)
         hist[i] = 0;
     const int lane = lane_id();
-    ChunkInfo f{~0u, 0u, ~0u, 0u, 0u, {0, 0, 0}};
+    ChunkInfo f = NOTHING_FOUND;
     // rows of 64 x UN consecutive elements per wave; lane l of row r holds
     // element 64 r + l, and the next element comes from the next lane
     constexpr int UN = KIND == RADIX_KEYS ? 8 : 4;
@@ -328,6 +365,9 @@ __global__ __launch_bounds__(COUNT_NT) void radix_count_first(RadixArgs a)
                     const bool eq = e[r].hi == nx.hi;
                     gt = gt || (eq && e[r].lo > nx.lo);
                     lt = lt || (eq && e[r].lo < nx.lo);
+                    // past the array's end an element meets itself
+                    f.near0 = min(f.near0, eq ? (e[r].lo ^ nx.lo) - 1 : ~0u);
+                    f.near1 = min(f.near1, (e[r].hi ^ nx.hi) - 1);
                     if (KIND == RADIX_PAIRS && i + 1 < a.n && e[r].lo > nx.lo)
                         f.flags |= VALUES_NOT_ASCENDING;
                 }
@@ -350,24 +390,15 @@ __global__ __launch_bounds__(COUNT_NT) void radix_count_first(RadixArgs a)
             }
         }
     }
-    f.and0 = wave_and(f.and0);
-    f.or0 = wave_or(f.or0);
-    f.and1 = wave_and(f.and1);
-    f.or1 = wave_or(f.or1);
-    f.flags = wave_or(f.flags);
+    f = wave_info(f);
     if (lane == 0)
         part[threadIdx.x / 64] = f;
     __syncthreads();
     if (threadIdx.x < RADIX)
         a.counts[(int64_t)blockIdx.x * RADIX + threadIdx.x] = hist_sum(hist, threadIdx.x);
     if (threadIdx.x == 0) {
-        for (int w = 1; w < COUNT_NT / 64; ++w) {
-            f.and0 &= part[w].and0;
-            f.or0 |= part[w].or0;
-            f.and1 &= part[w].and1;
-            f.or1 |= part[w].or1;
-            f.flags |= part[w].flags;
-        }
+        for (int w = 1; w < COUNT_NT / 64; ++w)
+            add_info(f, part[w]);
         ((ChunkInfo *)a.info)[blockIdx.x] = f;
     }
 }
@@ -482,24 +513,14 @@ __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64,
 {
     __shared__ ChunkInfo part[8];
     __shared__ uint32_t same[8];
-    ChunkInfo f{~0u, 0u, ~0u, 0u, 0u, {0, 0, 0}};
+    ChunkInfo f = NOTHING_FOUND;
     const ChunkInfo *info = (const ChunkInfo *)a.info;
-    for (int c = threadIdx.x; c < a.chunks; c += blockDim.x) {
-        const ChunkInfo g = info[c];
-        f.and0 &= g.and0;
-        f.or0 |= g.or0;
-        f.and1 &= g.and1;
-        f.or1 |= g.or1;
-        f.flags |= g.flags;
-    }
-    f.and0 = wave_and(f.and0);
-    f.or0 = wave_or(f.or0);
-    f.and1 = wave_and(f.and1);
-    f.or1 = wave_or(f.or1);
-    f.flags = wave_or(f.flags);
+    for (int c = threadIdx.x; c < a.chunks; c += blockDim.x)
+        add_info(f, info[c]);
+    f = wave_info(f);
     if (lane_id() == 0)
         part[threadIdx.x / 64] = f;
-    if (threadIdx.x < 8) {  // sampled pairs that first differ in digit threadIdx.x
+    if (threadIdx.x < 8) {  // sum of the runs' counts
         uint32_t c = 0;
         if (a.sample_pairs)
             for (int r = 0; r < a.sample_runs; ++r)
@@ -509,14 +530,9 @@ __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64,
     __syncthreads();
     if (threadIdx.x != 0)
         return;
-    for (int w = 1; w < (int)blockDim.x / 64; ++w) {
-        f.and0 &= part[w].and0;
-        f.or0 |= part[w].or0;
-        f.and1 &= part[w].and1;
-        f.or1 |= part[w].or1;
-        f.flags |= part[w].flags;
-    }
-    plan_sort(Found{f.flags, f.and0 ^ f.or0, f.and1 ^ f.or1, same,
+    for (int w = 1; w < (int)blockDim.x / 64; ++w)
+        add_info(f, part[w]);
+    plan_sort(Found{f.flags, f.and0 ^ f.or0, f.and1 ^ f.or1, f.near0, f.near1, same,
                     a.sample_pairs ? a.sample_runs : 0, a.n},
               passes, two, keys64, inplace, ctl);
 }
@@ -584,7 +600,9 @@ __global__ __launch_bounds__(512) void radix_scan(RadixArgs a, int pass, int pas
 // elements that are alike stand side by side and would never meet.)
 //
 // A workgroup draws a run, sorts it and counts its neighbours by the highest
-// digit in which they differ (equal neighbours are no pair to be told apart).
+// digit in which they differ (equal neighbours are no pair to be told apart; the
+// top digit is never left out, and its count gives way to that of the elements
+// that equal the one after next).
 // It runs after the first count, whose flags say whether the plan will ask:
 // 2^24 pairs with index values 341 -> 304 us, 2^26 1184 -> 1130.  Drawn by a
 // launch over the whole chip, sorted by the block sort and counted by a third
@@ -628,9 +646,10 @@ template <int KIND> __global__ __launch_bounds__(SAMPLE_LEN / 8) void radix_samp
         const int i = threadIdx.x + NT * j;
         const uint64_t d = i + 1 < SAMPLE_LEN ? (uint64_t)(Z[i] ^ Z[i + 1]) : 0;
         const int t = d ? (63 - __clzll((long long)d)) >> 3 : 8;
+        const bool third = i + 2 < SAMPLE_LEN && Z[i] == Z[i + 2];
 #pragma unroll
         for (int q = 0; q < 8; ++q)
-            count[q] += __popcll(__builtin_amdgcn_ballot_w64(t == q));
+            count[q] += __popcll(__builtin_amdgcn_ballot_w64(q == 7 ? third : t == q));
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q)

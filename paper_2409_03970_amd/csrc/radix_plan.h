@@ -30,7 +30,12 @@ enum { NOT_ASCENDING = 1, NOT_DESCENDING = 2, VALUES_NOT_ASCENDING = 4 };
 struct Found {
     uint32_t flags;
     uint32_t var0, var1;  // bits that differ between two elements: low word, high word
-    const uint32_t *same; // [8]: sampled neighbours that first differ in digit d
+    // smallest difference (xor, minus 1) between an element and the one after it in
+    // the input, over those that differ in the low word only, and in the high word
+    uint32_t near0, near1;
+    // [d < 7]: sampled neighbours that first differ in digit d; [7]: sampled
+    // elements equal to the one after next
+    const uint32_t *same;
     int runs;             // of the sample; 0: none was taken
     int64_t n;
 };
@@ -101,13 +106,24 @@ __host__ __device__ inline void scatter_modes(uint32_t *mode, uint32_t need, int
 // The highest digit of `need` stays: where nearly all elements are equal, no
 // sampled neighbours differ in it, but a round without a step would never
 // write the output.
+//
+// A sample does not see the few elements that differ from a heavy value by low
+// digits only, and one of them sends all the value's equals to the second
+// round.  So where one sampled element in 2,048 stands third or later among its
+// equals, no digit is left out that tells two neighbours of the input apart,
+// which a heavy value and its like are somewhere in an unordered input.
 __host__ __device__ inline uint32_t digits_to_drop(const Found &f, uint32_t need)
 {
     const double pairs = 0.5 * f.runs * SAMPLE_LEN * SAMPLE_LEN;
     const double at = 67108864.0 / (double)f.n;
     const double most = at >= 1.0 ? 0.5 : at >= 0.5 ? 0.5 * at : 0.25;
+    uint32_t limit = 7;
+    if ((double)f.same[7] * 2048.0 >= (double)f.runs * SAMPLE_LEN)
+        limit = f.near0 != ~0u   ? (31 - __builtin_clz(f.near0 + 1)) >> 3
+                : f.near1 != ~0u ? 4 + ((31 - __builtin_clz(f.near1 + 1)) >> 3)
+                                 : 0;
     uint32_t alike = 0, drop = 0;
-    for (uint32_t d = 1; d < 8 && need >> d; ++d) {
+    for (uint32_t d = 1; d <= limit && need >> d; ++d) {
         alike += f.same[d - 1];
         if ((double)alike * (double)f.n <= most * pairs)
             drop = d;

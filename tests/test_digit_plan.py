@@ -19,12 +19,13 @@ RUNS, N = 32, 1 << 24
 
 SHIM = """
 #include "radix_plan.h"
-extern "C" void plan(uint32_t flags, uint32_t var0, uint32_t var1, const uint32_t *same, int runs,
-                     int64_t n, int passes, int two, int keys64, int inplace, uint32_t *out)
+extern "C" void plan(uint32_t flags, uint32_t var0, uint32_t var1, uint32_t near0, uint32_t near1,
+                     const uint32_t *same, int runs, int64_t n, int passes, int two, int keys64,
+                     int inplace, uint32_t *out)
 {
     static_assert(sizeof(hvms::Ctl) == 83 * 4, "two rounds of eight steps of five words");
-    hvms::plan_sort(hvms::Found{flags, var0, var1, same, runs, n}, passes, two, keys64, inplace,
-                    (hvms::Ctl *)out);
+    hvms::plan_sort(hvms::Found{flags, var0, var1, near0, near1, same, runs, n}, passes, two,
+                    keys64, inplace, (hvms::Ctl *)out);
 }
 """
 
@@ -39,19 +40,27 @@ def plan(tmp_path_factory):
                     str(so)], check=True)
     f = ctypes.CDLL(str(so)).plan
 
-    def call(kind, x, drop, inplace, n=N):
+    def call(kind, x, drop, inplace, n=N, third=0):
         """The plan of sorting the uint64 words x with a sample that finds no two
-        elements alike without their lowest `drop` digits, and all with fewer."""
+        elements alike without their lowest `drop` digits, and all with fewer, and
+        `third` elements that equal the one after next."""
         two = kind != KEYS
         hi, lo = x >> np.uint64(32), x & np.uint64(0xffffffff)
         flags = (bool((x[:-1] > x[1:]).any()) * NOT_ASCENDING
                  | bool((x[:-1] < x[1:]).any()) * NOT_DESCENDING
                  | (kind == PAIRS and bool((lo[:-1] > lo[1:]).any())) * VALUES_NOT_ASCENDING)
-        same = (ctypes.c_uint32 * 8)(*[0 if d < drop else 8191 * RUNS for d in range(8)])
+        same = (ctypes.c_uint32 * 8)(*[0 if d < drop else 8191 * RUNS for d in range(7)], third)
+        near = [2**32 - 1] * 2
+        for a, b in zip(x[:-1], x[1:]):
+            d = int(a ^ b)
+            if d:
+                w = int(d >= 2**32)
+                near[w] = min(near[w], (d >> 32 * w) - 1)
         var = [int(np.bitwise_or.reduce(w ^ w[0])) for w in (lo, hi)]
         out = (ctypes.c_uint32 * 83)()
-        f(flags, var[0] if two else 0, var[1], same, RUNS if two else 0, ctypes.c_int64(n),
-          8 if two else 4, int(two), int(kind == KEYS64), int(inplace), out)
+        u = ctypes.c_uint32
+        f(flags, var[0] if two else 0, u(var[1]), u(near[0]), u(near[1]), same,
+          RUNS if two else 0, ctypes.c_int64(n), 8 if two else 4, int(two), int(kind == KEYS64), int(inplace), out)
         steps = np.array(out[:80]).reshape(2, 8, 5)
         return steps, out[80]
     return call
@@ -118,6 +127,24 @@ def test_every_plan_writes_the_output(plan, kind, inplace):
             z = _run(steps[1], y, kind, True)
             assert z is not None and np.array_equal(z, np.sort(x)), (need, drop, low)
     assert (dropped > 500) == (kind != KEYS)
+
+
+@pytest.mark.parametrize("kind", (PAIRS, KEYS64))
+@pytest.mark.parametrize("digit", range(8))
+def test_heavy_value_and_its_like(plan, kind, digit):
+    """Mostly one value, in all eight digits another now and then, and one element
+    that differs from its neighbour from `digit` on: with many equal elements in the
+    sample no digit above that one is left out, and with few the sample decides."""
+    x = np.full(24, 0x0102030405060708, dtype=np.uint64)
+    x[3], x[4] = 0xf1f2f3f4f5f6f7f8, 0                    # the top digit varies
+    x[11] ^= np.uint64(3) << np.uint64(8 * digit)
+    x[20] ^= np.uint64(0xff) << np.uint64(56)
+    many = -(-RUNS * 8192 // 2048)
+    assert plan(kind, x, 7, False, third=many)[1] == (digit if digit >= 2 else 0)
+    assert plan(kind, x, 7, False, third=many - 1)[1] == 7
+    y = x[x != x[11]]                                     # no like of the heavy value
+    assert plan(kind, y, 7, False, third=many)[1] == 7
+    assert plan(kind, x, 1, False, third=many)[1] == 0
 
 
 @pytest.mark.parametrize("inplace", (False, True))
