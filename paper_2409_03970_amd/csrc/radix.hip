@@ -671,8 +671,8 @@ template <int KIND> __global__ __launch_bounds__(SAMPLE_LEN / 8) void radix_samp
 // the common digits of its group, does not change.  Bound by one read of the
 // elements (2^28 uniform pairs, 12 % of them alike: 2.5 ms when the first
 // lane of each group read it through in memory, now 1.0).
-constexpr int GROUP_MAX = 8192;    // elements of a listed group: one block-sort tile
-constexpr int GROUPS_MAX = 65536;  // listed groups
+constexpr int GROUP_MAX = 16384;    // elements of a listed group: the LDS of one workgroup
+constexpr int GROUPS_MAX = 131072;  // listed groups
 
 template <int KIND> __device__ __forceinline__ uint64_t finish_elem(const RadixArgs &a, int64_t i)
 {
@@ -796,35 +796,117 @@ template <int KIND> __global__ __launch_bounds__(256) void radix_finish(RadixArg
     }
 }
 
-// Sorts the listed groups, each as one padded tile of the block sort.
+// A listed group of at most 64 ROWS elements, by one wave: every element's
+// position is the number of elements before it, counted against each in turn.
+template <int KIND, int ROWS>
+__device__ __forceinline__ void wave_group(const RadixArgs &a, int64_t i0, int len)
+{
+    const int lane = lane_id();
+    uint64_t x[ROWS];
+    int at[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const int i = 64 * r + lane;
+        x[r] = finish_elem<KIND>(a, i0 + (i < len ? i : 0));
+        at[r] = 0;
+    }
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q) {
+        const int m = len - 64 * q < 64 ? len - 64 * q : 64;
+        for (int j = 0; j < m; ++j) {  // element 64 q + j; equal ones keep their order
+            const uint64_t y =
+                (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(x[q] >> 32), j) << 32 |
+                (uint32_t)__builtin_amdgcn_readlane((int)x[q], j);
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r)
+                at[r] += r < q ? y < x[r] : r > q ? y <= x[r] : lane > j ? y <= x[r] : y < x[r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+        if (64 * r + lane < len)
+            finish_store<KIND>(a, i0 + at[r], x[r]);
+}
+
+// Part of a listed group, at most one padded tile of the block sort.
+constexpr int GROUP_TILE = GROUP_MAX / 2;
+template <int KIND>
+__device__ __forceinline__ void tile_group(const RadixArgs &a, int64_t *S, int64_t i0, int len)
+{
+    constexpr int NT = 1024, R = GROUP_TILE / NT;
+    const LdsSkew<int64_t> Z{S, 0};
+    int64_t v[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int i = (threadIdx.x >> 6) * (64 * R) + 64 * j + (threadIdx.x & 63);
+        // unsigned order to signed; pads sort last
+        v[j] = i < len ? (int64_t)(finish_elem<KIND>(a, i0 + i) ^ (1ull << 63))
+                       : Traits<int64_t>::kMax;
+    }
+    sort_tile_core<R, NT, int64_t, 0>(S, v, threadIdx.x, 6, 4);
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int i = threadIdx.x + NT * j;
+        if (i < len)
+            finish_store<KIND>(a, i0 + i, (uint64_t)Z[i] ^ (1ull << 63));
+    }
+    __syncthreads();
+}
+
+// A group of two sorted parts: every element's position is its own in its part
+// and its rank in the other.
+template <int KIND>
+__device__ __forceinline__ void merge_group(const RadixArgs &a, uint64_t *S, int64_t i0, int len)
+{
+    for (int i = threadIdx.x; i < len; i += 1024)
+        S[i] = finish_elem<KIND>(a, i0 + i);
+    __syncthreads();
+    for (int i = threadIdx.x; i < len; i += 1024) {
+        const bool first = i < GROUP_TILE;
+        const uint64_t x = S[i];
+        int lo = first ? GROUP_TILE : 0, hi = first ? len : GROUP_TILE;
+        while (lo < hi) {  // equal elements of the first part come first
+            const int mid = (lo + hi) >> 1;
+            const bool before = first ? S[mid] < x : S[mid] <= x;
+            lo = before ? mid + 1 : lo;
+            hi = before ? hi : mid;
+        }
+        finish_store<KIND>(a, i0 + i + lo - GROUP_TILE, x);
+    }
+    __syncthreads();
+}
+
+// Sorts the listed groups: a wave each those of up to WAVE_GROUP elements, then
+// a workgroup each the others.  What the finish lists is mostly little more than
+// half a window: 9,232 groups of about 40 pairs (2^27 pairs of mixture keys and
+// random values, without two digits) took 810 us as padded tiles, now 26.
+constexpr int WAVE_GROUP = 256;
 template <int KIND> __global__ __launch_bounds__(1024) void radix_groups(RadixArgs a)
 {
-    constexpr int R = 8, NT = GROUP_MAX / R;
     const Ctl *ctl = (const Ctl *)a.ctl;
     if (ctl->drop == 0 || ctl->again)
         return;
-    __shared__ __attribute__((aligned(16))) int64_t S[LdsSkew<int64_t>::size(R * NT)];
-    const LdsSkew<int64_t> Z{S, 0};
+    __shared__ __attribute__((aligned(16))) int64_t S[GROUP_MAX];
+    static_assert(LdsSkew<int64_t>::size(GROUP_TILE) <= GROUP_MAX, "a tile fits");
     const uint32_t count = ctl->groups < GROUPS_MAX ? ctl->groups : GROUPS_MAX;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+    for (uint32_t g = blockIdx.x * 16 + wave; g < count; g += gridDim.x * 16) {
+        const int64_t i0 = a.groups[g].x;
+        const int len = __builtin_amdgcn_readfirstlane((int)a.groups[g].y);
+        if (len <= 64)
+            wave_group<KIND, 1>(a, i0, len);
+        else if (len <= WAVE_GROUP)
+            wave_group<KIND, WAVE_GROUP / 64>(a, i0, len);
+    }
     for (uint32_t g = blockIdx.x; g < count; g += gridDim.x) {
         const int64_t i0 = a.groups[g].x;
         const int len = (int)a.groups[g].y;
-        int64_t v[R];
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int i = (threadIdx.x >> 6) * (64 * R) + 64 * j + (threadIdx.x & 63);
-            // unsigned order to signed; pads sort last
-            v[j] = i < len ? (int64_t)(finish_elem<KIND>(a, i0 + i) ^ (1ull << 63))
-                           : Traits<int64_t>::kMax;
-        }
-        sort_tile_core<R, NT, int64_t, 0>(S, v, threadIdx.x, 6, 4);
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int i = threadIdx.x + NT * j;
-            if (i < len)
-                finish_store<KIND>(a, i0 + i, (uint64_t)Z[i] ^ (1ull << 63));
-        }
-        __syncthreads();
+        if (len <= WAVE_GROUP)
+            continue;
+        for (int i = 0; i < len; i += GROUP_TILE)
+            tile_group<KIND>(a, S, i0 + i, len - i < GROUP_TILE ? len - i : GROUP_TILE);
+        if (len > GROUP_TILE)
+            merge_group<KIND>(a, (uint64_t *)S, i0, len);
     }
 }
 
@@ -1402,7 +1484,7 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
         if (a.sample_pairs) {
             hipLaunchKernelGGL(radix_finish<KIND>, dim3((unsigned)((a.n + 2047) / 2048)),
                                dim3(256), 0, s, a);
-            hipLaunchKernelGGL(radix_groups<KIND>, dim3(2 * device_cus()), dim3(1024), 0, s, a);
+            hipLaunchKernelGGL(radix_groups<KIND>, dim3(device_cus()), dim3(1024), 0, s, a);
             a.round = 1;  // the second round sorts the output, in place
             a.k[B_IN] = a.k[B_OUT];
             a.v[B_IN] = a.v[B_OUT];

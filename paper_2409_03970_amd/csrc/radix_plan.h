@@ -95,13 +95,14 @@ __host__ __device__ inline void scatter_modes(uint32_t *mode, uint32_t need, int
 }
 
 // The low digits the first round leaves out, out of those in `need`: the most
-// without which the sample leaves an element alike with at most half another
-// one on average, a quarter from 2^27 elements on.  m elements in groups of g
-// are m g / n of that, so groups of more than GROUP_MAX elements slip through
-// only where there are few, and groups that fill the list (longer than half a
-// window) are GROUPS_MAX * 33^2 / n of it or more.  Pairs of mixture keys and
-// random values, between the two: 2^26 2.83 ms with all eight passes, 2.46
-// with six; 2^27 5.75 and 5.95, where 9,232 groups were listed.
+// without which the sample leaves an element alike with at most `most` other
+// ones on average, half a one up to 2^26 elements, one from 2^27 on.  m elements
+// in groups of g are m g / n of that, so one group of more than GROUP_MAX
+// elements is over the line up to 2^28, and groups that fill the list (longer
+// than half a window) are GROUPS_MAX * 33^2 / n of it or more.  Pairs of mixture
+// keys and random values, whose one key in 55 is the largest: 2^27 5.65 ms with
+// all eight passes, 5.15 with six and about 9,000 listed groups (merge sort
+// 5.42), 10^8 4.24 and 3.67; at 2^28, 65,536 groups, 11.9 and 12.4.
 //
 // The highest digit of `need` stays: where nearly all elements are equal, no
 // sampled neighbours differ in it, but a round without a step would never
@@ -115,8 +116,8 @@ __host__ __device__ inline void scatter_modes(uint32_t *mode, uint32_t need, int
 __host__ __device__ inline uint32_t digits_to_drop(const Found &f, uint32_t need)
 {
     const double pairs = 0.5 * f.runs * SAMPLE_LEN * SAMPLE_LEN;
-    const double at = 67108864.0 / (double)f.n;
-    const double most = at >= 1.0 ? 0.5 : at >= 0.5 ? 0.5 * at : 0.25;
+    const double part = (double)f.n / 134217728.0;
+    const double most = part <= 0.5 ? 0.5 : part <= 1.0 ? part : 1.0;
     uint32_t limit = 7;
     if ((double)f.same[7] * 2048.0 >= (double)f.runs * SAMPLE_LEN)
         limit = f.near0 != ~0u   ? (31 - __builtin_clz(f.near0 + 1)) >> 3

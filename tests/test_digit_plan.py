@@ -40,7 +40,7 @@ def plan(tmp_path_factory):
                     str(so)], check=True)
     f = ctypes.CDLL(str(so)).plan
 
-    def call(kind, x, drop, inplace, n=N, third=0):
+    def call(kind, x, drop, inplace, n=N, third=0, alike=None):
         """The plan of sorting the uint64 words x with a sample that finds no two
         elements alike without their lowest `drop` digits, and all with fewer, and
         `third` elements that equal the one after next."""
@@ -50,6 +50,8 @@ def plan(tmp_path_factory):
                  | bool((x[:-1] < x[1:]).any()) * NOT_DESCENDING
                  | (kind == PAIRS and bool((lo[:-1] > lo[1:]).any())) * VALUES_NOT_ASCENDING)
         same = (ctypes.c_uint32 * 8)(*[0 if d < drop else 8191 * RUNS for d in range(7)], third)
+        for d, count in enumerate(alike or ()):
+            same[d] = count
         near = [2**32 - 1] * 2
         for a, b in zip(x[:-1], x[1:]):
             d = int(a ^ b)
@@ -145,6 +147,15 @@ def test_heavy_value_and_its_like(plan, kind, digit):
     y = x[x != x[11]]                                     # no like of the heavy value
     assert plan(kind, y, 7, False, third=many)[1] == 7
     assert plan(kind, x, 1, False, third=many)[1] == 0
+
+
+@pytest.mark.parametrize("n,most", ((1 << 24, 0.5), (1 << 26, 0.5), (3 << 25, 0.75), (1 << 27, 1.0),
+                                    (1 << 28, 1.0)))
+def test_how_much_may_be_left_alike(plan, n, most):
+    x = _words(255, np.random.default_rng(3))
+    line = int(most * RUNS * 8192**2 / 2 / n)             # sampled neighbours alike
+    for alike, low in ((line, 7), (line + 1, 2)):
+        assert plan(KEYS64, x, 7, False, n=n, third=0, alike=(0, 0, alike))[1] == low
 
 
 @pytest.mark.parametrize("inplace", (False, True))
