@@ -1436,6 +1436,18 @@ RadixLayout radix_layout(int kind, int64_t n)
     return w;
 }
 
+// One launch of a sort.  Each reads what the ones before wrote (positions from
+// counts), so after one that failed nothing more is enqueued.
+template <typename... P, typename... Args>
+static void launch(hipError_t &e, void (*kernel)(P...), dim3 grid, int threads, hipStream_t s,
+                   Args... args)
+{
+    if (e != hipSuccess)
+        return;
+    hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, s, args...);
+    e = hipGetLastError();
+}
+
 // WAVES: waves per SIMD the registers are kept to; WGS: workgroups per CU.
 template <int KIND, int SHAPE, int WAVES, int WGS>
 static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
@@ -1444,6 +1456,7 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
     constexpr bool two = KIND == RADIX_PAIRS || KIND == RADIX_KEYS64;
     constexpr bool keys64 = KIND == RADIX_KEYS64;
     constexpr int passes = two ? 8 : 4;
+    hipError_t e = hipSuccess;
     a.tiles = (a.n + T - 1) / T;
     a.per_log2 = chunk_log2(a.tiles);
     a.chunks = (int)((a.tiles + ((int64_t)1 << a.per_log2) - 1) >> a.per_log2);
@@ -1452,13 +1465,13 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
             const dim3 grid((unsigned)a.tiles);
             for (int p = 0; p < passes; ++p) {
                 if (p == 0)
-                    hipLaunchKernelGGL((radix_count_first<KIND, T>), grid, dim3(COUNT_NT), 0, s, a);
+                    launch(e, radix_count_first<KIND, T>, grid, COUNT_NT, s, a);
                 else
-                    hipLaunchKernelGGL((radix_count<KIND, T>), grid, dim3(COUNT_NT), 0, s, a, p);
-                hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, OF_TILES>), grid, dim3(NT),
-                                   0, s, a, p, (int)inplace);
+                    launch(e, radix_count<KIND, T>, grid, COUNT_NT, s, a, p);
+                launch(e, radix_scatter<NT, K, KIND, WAVES, OF_TILES>, grid, NT, s, a, p,
+                       (int)inplace);
             }
-            return hipGetLastError();
+            return e;
         }
     }
     const int64_t fit = (int64_t)device_cus() * WGS;
@@ -1467,35 +1480,31 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
     const dim3 cgrid((unsigned)a.chunks), sgrid((unsigned)wg);
     for (int p = 0; p < passes; ++p) {
         if (p == 0)
-            hipLaunchKernelGGL((radix_count_first<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a);
+            launch(e, radix_count_first<KIND, T>, cgrid, COUNT_NT, s, a);
         else
-            hipLaunchKernelGGL((radix_count<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a, p);
+            launch(e, radix_count<KIND, T>, cgrid, COUNT_NT, s, a, p);
         if constexpr (two) {
             if (p == 0 && a.sample_pairs)
-                hipLaunchKernelGGL(radix_sample<KIND>, dim3(a.sample_runs), dim3(SAMPLE_LEN / 8), 0,
-                                   s, a);
+                launch(e, radix_sample<KIND>, dim3(a.sample_runs), SAMPLE_LEN / 8, s, a);
         }
-        hipLaunchKernelGGL(radix_scan, dim3(RADIX / 16 + (p == 0)), dim3(512), 0, s, a, p, passes,
-                           (int)two, (int)keys64, (int)inplace);
-        hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, OF_SCAN>), sgrid, dim3(NT), 0, s, a,
-                           p, (int)inplace);
+        launch(e, radix_scan, dim3(RADIX / 16 + (p == 0)), 512, s, a, p, passes, (int)two,
+               (int)keys64, (int)inplace);
+        launch(e, radix_scatter<NT, K, KIND, WAVES, OF_SCAN>, sgrid, NT, s, a, p, (int)inplace);
     }
     if constexpr (two) {
         if (a.sample_pairs) {
-            hipLaunchKernelGGL(radix_finish<KIND>, dim3((unsigned)((a.n + 2047) / 2048)),
-                               dim3(256), 0, s, a);
-            hipLaunchKernelGGL(radix_groups<KIND>, dim3(device_cus()), dim3(1024), 0, s, a);
+            launch(e, radix_finish<KIND>, dim3((unsigned)((a.n + 2047) / 2048)), 256, s, a);
+            launch(e, radix_groups<KIND>, dim3(device_cus()), 1024, s, a);
             a.round = 1;  // the second round sorts the output, in place
             a.k[B_IN] = a.k[B_OUT];
             a.v[B_IN] = a.v[B_OUT];
             for (int p = 0; p < passes; ++p) {
-                hipLaunchKernelGGL((radix_count<KIND, T>), cgrid, dim3(COUNT_NT), 0, s, a, p);
-                hipLaunchKernelGGL((radix_scatter<NT, K, KIND, WAVES, OF_CHUNKS>), sgrid, dim3(NT),
-                                   0, s, a, p, 1);
+                launch(e, radix_count<KIND, T>, cgrid, COUNT_NT, s, a, p);
+                launch(e, radix_scatter<NT, K, KIND, WAVES, OF_CHUNKS>, sgrid, NT, s, a, p, 1);
             }
         }
     }
-    return hipGetLastError();
+    return e;
 }
 
 hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap km,

@@ -1,0 +1,74 @@
+"""A launch that fails ends the call: the launches after it read what it should
+have written (counts, positions), so none of them may be enqueued.  The library
+runs in a process of its own on a stand-in for the HIP calls that launch."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+import paper_2409_03970_amd as hv
+
+pytestmark = pytest.mark.skipif(not os.path.exists(hv.LIB_PATH), reason="libhvms.so not built")
+
+STAND_IN = r"""
+static int launches, fail_at, last;
+int hipLaunchKernel(const void *f, ...) { return ++launches == fail_at ? (last = 2) : 0; }
+int hipGetLastError(void) { int e = last; last = 0; return e; }
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipDeviceGetAttribute(int *v, int a, int d) { *v = 256; return 0; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int b, unsigned long s)
+{ *n = 1; return 0; }
+int __hipPushCallConfiguration() { return 0; }
+int __hipPopCallConfiguration() { return 0; }
+void begin(int k) { launches = 0; fail_at = k; last = 0; }
+int attempted(void) { return launches; }
+"""
+
+RUN = r"""
+import ctypes, sys
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+L = ctypes.CDLL(sys.argv[2])
+V, I = ctypes.c_void_p, ctypes.c_int64
+P = [V(i << 40) for i in range(1, 6)]          # arrays that are never touched
+for f in ("hvms_sort_workspace_bytes", "hvms_sort64_workspace_bytes",
+          "hvms_sort_by_key_workspace_bytes"):
+    getattr(L, f).restype = I
+
+def call(kind, n):
+    if kind == "keys":
+        need = L.hvms_sort_workspace_bytes(I(n), 0, None)
+        return L.hvms_sort_i32(P[0], P[1], I(n), P[4], ctypes.c_size_t(need), None, None)
+    if kind == "pairs":
+        need = L.hvms_sort_workspace_bytes(I(n), 1, None)
+        return L.hvms_sort_pairs_i32(*P[:4], I(n), P[4], ctypes.c_size_t(need), None, None)
+    if kind == "i64":
+        need = L.hvms_sort64_workspace_bytes(I(n), None)
+        return L.hvms_sort_i64(P[0], P[1], I(n), P[4], ctypes.c_size_t(need), None, None)
+    need = L.hvms_sort_by_key_workspace_bytes(I(n), None)
+    return L.hvms_sort_by_key_i32_p64(*P[:4], I(n), P[4], ctypes.c_size_t(need), None, None)
+
+for kind, n in (("keys", 1000), ("keys", 40000), ("keys", 1 << 20), ("keys", 1 << 27),
+                ("by_key", 1 << 17), ("by_key", 1 << 20), ("pairs", 100000), ("pairs", 1 << 22),
+                ("pairs", 1 << 24), ("i64", 1 << 22), ("i64", 1 << 26)):
+    shim.begin(0)
+    assert call(kind, n) == 0, (kind, n)
+    total = shim.attempted()
+    assert total >= 1
+    for k in range(1, total + 1):
+        shim.begin(k)
+        status = call(kind, n)
+        assert (status, shim.attempted()) == (-3, k), (kind, n, total, k, status,
+                                                       shim.attempted())
+print("ok")
+"""
+
+
+def test_nothing_is_enqueued_after_a_failed_launch(tmp_path):
+    src, so, run = tmp_path / "shim.c", tmp_path / "shim.so", tmp_path / "run.py"
+    src.write_text(STAND_IN)
+    run.write_text(RUN)
+    subprocess.run(["gcc", "-shared", "-fPIC", "-w", str(src), "-o", str(so)], check=True)
+    r = subprocess.run([sys.executable, str(run), str(so), hv.LIB_PATH], capture_output=True,
+                       text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
