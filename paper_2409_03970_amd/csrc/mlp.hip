@@ -420,6 +420,9 @@ int hvms_cdf_backward(const float *d_params, const float *d_x, const float *d_t,
     hipLaunchKernelGGL(cdf_grad_kernel<false>, dim3(rows), dim3(256), 0, (hipStream_t)stream,
                        d_params, d_x, d_t, nullptr, (int64_t)0, (uint64_t)0, (uint64_t)0, b,
                        partial);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return status(e);
     hipLaunchKernelGGL(cdf_reduce_kernel<false>, dim3((NP + 64) / 64), dim3(1024), 0,
                        (hipStream_t)stream, partial, rows, b, d_grad, d_loss, AdamArgs{});
     return status(hipGetLastError());
@@ -459,17 +462,20 @@ int hvms_cdf_train(float *d_params, float *d_m, float *d_v, const int32_t *d_sor
     float *partial = (float *)(ws + w.bwd + bwd_layout(batch).partial);
     const int rows = grad_rows(batch);
     hipLaunchKernelGGL(cdf_zero_kernel, dim3((NP + 255) / 256), dim3(256), 0, s, d_m, d_v);
-    for (int step = 1; step <= steps; ++step) {
+    st = status(hipGetLastError());
+    for (int step = 1; step <= steps && !st; ++step) {
         hipLaunchKernelGGL(cdf_grad_kernel<true>, dim3(rows), dim3(256), 0, s, d_params, nullptr,
                            nullptr, d_sorted, m, seed, (uint64_t)(step - 1), batch, partial);
+        // no Adam step on partials that were not written
+        st = status(hipGetLastError());
+        if (st)
+            return st;
         hipLaunchKernelGGL(cdf_reduce_kernel<true>, dim3((NP + 64) / 64), dim3(1024), 0, s,
                            partial, rows, batch, nullptr, nullptr,
                            adam_args(d_params, d_m, d_v, step, lr, 0.9f, 0.999f, 1e-8f));
         st = status(hipGetLastError());
-        if (st)
-            return st;
     }
-    return HVMS_OK;
+    return st;
 }
 
 int hvms_cdf_sample_i32(const int32_t *d_keys, int64_t n, int64_t m, uint64_t seed,

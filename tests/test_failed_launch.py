@@ -1,5 +1,5 @@
 """A launch that fails ends the call: the launches after it read what it should
-have written (counts, positions), so none of them may be enqueued.  The library
+have written (counts, positions, gradients), so none of them may be enqueued.  The library
 runs in a process of its own on a stand-in for the HIP calls that launch."""
 import os
 import subprocess
@@ -32,7 +32,8 @@ L = ctypes.CDLL(sys.argv[2])
 V, I = ctypes.c_void_p, ctypes.c_int64
 P = [V(i << 40) for i in range(1, 6)]          # arrays that are never touched
 for f in ("hvms_sort_workspace_bytes", "hvms_sort64_workspace_bytes",
-          "hvms_sort_by_key_workspace_bytes"):
+          "hvms_sort_by_key_workspace_bytes", "hvms_cdf_workspace_bytes",
+          "hvms_cdf_train_workspace_bytes"):
     getattr(L, f).restype = I
 
 def call(kind, n):
@@ -45,12 +46,20 @@ def call(kind, n):
     if kind == "i64":
         need = L.hvms_sort64_workspace_bytes(I(n), None)
         return L.hvms_sort_i64(P[0], P[1], I(n), P[4], ctypes.c_size_t(need), None, None)
+    if kind == "backward":
+        need = L.hvms_cdf_workspace_bytes(I(n))
+        return L.hvms_cdf_backward(*P[:4], P[3], I(n), P[4], ctypes.c_size_t(need), None)
+    if kind == "train":
+        need = L.hvms_cdf_train_workspace_bytes(I(n))
+        return L.hvms_cdf_train(*P[:4], I(1000), I(n), 3, ctypes.c_float(1e-3),
+                                ctypes.c_uint64(1), P[4], ctypes.c_size_t(need), None)
     need = L.hvms_sort_by_key_workspace_bytes(I(n), None)
     return L.hvms_sort_by_key_i32_p64(*P[:4], I(n), P[4], ctypes.c_size_t(need), None, None)
 
 for kind, n in (("keys", 1000), ("keys", 40000), ("keys", 1 << 20), ("keys", 1 << 27),
                 ("by_key", 1 << 17), ("by_key", 1 << 20), ("pairs", 100000), ("pairs", 1 << 22),
-                ("pairs", 1 << 24), ("i64", 1 << 22), ("i64", 1 << 26)):
+                ("pairs", 1 << 24), ("i64", 1 << 22), ("i64", 1 << 26),
+                ("backward", 1000), ("train", 1000)):
     shim.begin(0)
     assert call(kind, n) == 0, (kind, n)
     total = shim.attempted()
