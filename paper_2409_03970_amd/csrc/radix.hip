@@ -491,6 +491,15 @@ __global__ __launch_bounds__(COUNT_NT) void radix_count(RadixArgs a, int pass)
         a.counts[(int64_t)blockIdx.x * RADIX + threadIdx.x] = hist_sum(hist, threadIdx.x);
 }
 
+// Orders one wave's LDS operations before those after, also where they go through
+// other types: the hardware completes them in order, so only the compiler has to
+// keep them so.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // -------------------------------------------------------------------- scan
 
 // Inclusive prefix sum over the lanes of a wave (row shifts, then the row
@@ -1155,6 +1164,7 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
 
         // ranks among the wave's keys of the same digit, two to a register
         *(uint2 *)&cnt[wave][4 * lane] = make_uint2(0, 0);
+        wave_lds_fence();
         uint32_t pos[K / 2];
         if (loose && cnt_valid == T) {
             // an LDS atomic per key, in no order among a row's lanes
@@ -1186,11 +1196,8 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
                     pos[k / 2] = c + before;
                 if (before == 0)
                     cnt[wave][d] = (uint16_t)(c + all);
-                // the next row's reads follow this row's writes of other lanes:
-                // one wave's LDS operations complete in order, so only the
-                // compiler has to keep them so
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
+                // the next row's reads follow this row's writes of other lanes
+                wave_lds_fence();
                 __builtin_amdgcn_sched_barrier(0);  // one row's masks at a time
             }
         }
@@ -1232,6 +1239,7 @@ __global__ __launch_bounds__(NT, WAVES) void radix_scatter(RadixArgs a, int pass
             }
             *(uint2 *)&off[wave][4 * lane] =
                 make_uint2(mine[0] | (mine[1] << 16), mine[2] | (mine[3] << 16));
+            wave_lds_fence();
         }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
