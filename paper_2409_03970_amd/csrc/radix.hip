@@ -189,15 +189,18 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t x)
         x = min(x, (uint32_t)__shfl_xor((int)x, d));
     return x;
 }
-__device__ __forceinline__ ChunkInfo wave_info(ChunkInfo f)
+// (Keys alone have no low word, and no digits to leave out.)
+__device__ __forceinline__ ChunkInfo wave_info(ChunkInfo f, bool two)
 {
-    f.and0 = wave_and(f.and0);
-    f.or0 = wave_or(f.or0);
     f.and1 = wave_and(f.and1);
     f.or1 = wave_or(f.or1);
     f.flags = wave_or(f.flags);
-    f.near0 = wave_min(f.near0);
-    f.near1 = wave_min(f.near1);
+    if (two) {
+        f.and0 = wave_and(f.and0);
+        f.or0 = wave_or(f.or0);
+        f.near0 = wave_min(f.near0);
+        f.near1 = wave_min(f.near1);
+    }
     return f;
 }
 __device__ __forceinline__ void add_info(ChunkInfo &f, const ChunkInfo &g)
@@ -390,7 +393,7 @@ __global__ __launch_bounds__(COUNT_NT) void radix_count_first(RadixArgs a)
             }
         }
     }
-    f = wave_info(f);
+    f = wave_info(f, KIND == RADIX_PAIRS || KIND == RADIX_KEYS64);
     if (lane == 0)
         part[threadIdx.x / 64] = f;
     __syncthreads();
@@ -526,7 +529,7 @@ __device__ void make_plan(const RadixArgs &a, int passes, bool two, bool keys64,
     const ChunkInfo *info = (const ChunkInfo *)a.info;
     for (int c = threadIdx.x; c < a.chunks; c += blockDim.x)
         add_info(f, info[c]);
-    f = wave_info(f);
+    f = wave_info(f, two);
     if (lane_id() == 0)
         part[threadIdx.x / 64] = f;
     if (threadIdx.x < 8) {  // sum of the runs' counts
