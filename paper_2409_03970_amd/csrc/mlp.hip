@@ -134,19 +134,19 @@ __global__ __launch_bounds__(256, 1) void cdf_grad_kernel(
         gw1[r] = gb1[r] = gb2[r] = gw3[r] = gw2[r] = 0.0f;
 
     for (int64_t i0 = (int64_t)blockIdx.x * CHUNK; i0 < b; i0 += (int64_t)gridDim.x * CHUNK) {
-        const int64_t i = i0 + wave * 32 + s;
-        const bool in = i < b;
-        float xi = 0.0f, ti = 0.0f;
-        if (in) {
-            if constexpr (TRAIN) {
-                const int64_t k =
-                    (int64_t)(splitmix64(seed, (step << 32) + (uint64_t)i) % (uint64_t)m);
-                xi = key_to_unit(sorted[k]);
-                ti = (float)((double)k / (double)m);
-            } else {
-                xi = x[i];
-                ti = tgt[i];
-            }
+        // lanes past the last sample repeat it with dy = 0: their products with
+        // its activations are finite wherever its own gradient is
+        const bool in = i0 + wave * 32 + s < b;
+        const int64_t i = in ? i0 + wave * 32 + s : b - 1;
+        float xi, ti;
+        if constexpr (TRAIN) {
+            const int64_t k =
+                (int64_t)(splitmix64(seed, (step << 32) + (uint64_t)i) % (uint64_t)m);
+            xi = key_to_unit(sorted[k]);
+            ti = (float)((double)k / (double)m);
+        } else {
+            xi = x[i];
+            ti = tgt[i];
         }
         float h1[16];
         f32x16 z2;
