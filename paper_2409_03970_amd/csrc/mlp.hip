@@ -25,7 +25,6 @@ namespace {
 
 constexpr int H = 32;
 constexpr int NP = HVMS_CDF_PARAMS;  // 1153
-constexpr int NREC = 4 + 4 * H;      // floats per sample the workspace is sized by
 constexpr int CHUNK = 128;           // samples a workgroup takes at a time (4 waves x 32)
 constexpr int GRAD_WGS = 256;        // rows of partials at most: one workgroup per CU
 
@@ -313,25 +312,25 @@ __global__ __launch_bounds__(256) void cdf_sample_kernel(const int32_t *__restri
         out[k] = keys[splitmix64(seed, (uint64_t)k) % (uint64_t)n];
 }
 
-// The workspace is sized by NREC floats per sample and a row of partials per
-// CHUNK of them; the kernels use the rows of at most GRAD_WGS workgroups.
-struct BwdWs {
-    int64_t partial, total;
-};
-
-BwdWs bwd_layout(int64_t b)
-{
-    BwdWs w;
-    const int64_t nchunks = (b + CHUNK - 1) / CHUNK;
-    w.partial = ((NREC * b * 4) + 255) & ~(int64_t)255;
-    w.total = w.partial + (((nchunks * (NP + 1) * 4) + 255) & ~(int64_t)255);
-    return w;
-}
-
+// Rows of partials of a batch, which are all that its workspace holds.
 int grad_rows(int64_t b)
 {
-    const int64_t chunks = (b + CHUNK - 1) / CHUNK;
+    const int64_t chunks = b / CHUNK + (b % CHUNK != 0);
     return (int)(chunks < GRAD_WGS ? chunks : GRAD_WGS);
+}
+
+int64_t partial_bytes(int64_t b)
+{
+    return ((int64_t)grad_rows(b) * (NP + 1) * 4 + 255) & ~(int64_t)255;
+}
+
+// What hvms_cdf_backward has always asked for: 132 floats a sample and a row
+// of partials for each CHUNK of them.
+int64_t backward_bytes(int64_t b)
+{
+    const int64_t chunks = (b + CHUNK - 1) / CHUNK;
+    return ((132 * b * 4 + 255) & ~(int64_t)255) +
+           ((chunks * (NP + 1) * 4 + 255) & ~(int64_t)255);
 }
 
 AdamArgs adam_args(float *p, float *m, float *v, int step, float lr, float beta1, float beta2,
@@ -339,19 +338,6 @@ AdamArgs adam_args(float *p, float *m, float *v, int step, float lr, float beta1
 {
     return {p, m, v, lr, beta1, beta2, eps, (float)(1.0 - pow((double)beta1, (double)step)),
             (float)(1.0 - pow((double)beta2, (double)step))};
-}
-
-struct TrainWs {
-    int64_t bwd, total;
-};
-
-TrainWs train_layout(int64_t batch)
-{
-    TrainWs w;
-    auto a = [](int64_t v) { return (v + 255) & ~(int64_t)255; };
-    w.bwd = 2 * a(batch * 4) + a(NP * 4) + 256;  // bytes before it: unused
-    w.total = w.bwd + bwd_layout(batch).total;
-    return w;
 }
 
 int status(hipError_t e)
@@ -404,7 +390,7 @@ int64_t hvms_cdf_workspace_bytes(int64_t b)
 {
     if (b < 0)
         return HVMS_ERR_INVALID_ARG;
-    return bwd_layout(b).total;
+    return backward_bytes(b);
 }
 
 int hvms_cdf_backward(const float *d_params, const float *d_x, const float *d_t, float *d_grad,
@@ -412,10 +398,10 @@ int hvms_cdf_backward(const float *d_params, const float *d_x, const float *d_t,
 {
     if (b <= 0 || !d_params || !d_x || !d_t || !d_grad || !d_loss)
         return HVMS_ERR_INVALID_ARG;
-    const int st = check(d_ws, ws_bytes, bwd_layout(b).total);
+    const int st = check(d_ws, ws_bytes, backward_bytes(b));
     if (st)
         return st;
-    float *partial = (float *)((char *)d_ws + bwd_layout(b).partial);
+    float *partial = (float *)d_ws;
     const int rows = grad_rows(b);
     hipLaunchKernelGGL(cdf_grad_kernel<false>, dim3(rows), dim3(256), 0, (hipStream_t)stream,
                        d_params, d_x, d_t, nullptr, (int64_t)0, (uint64_t)0, (uint64_t)0, b,
@@ -444,7 +430,7 @@ int64_t hvms_cdf_train_workspace_bytes(int64_t batch)
 {
     if (batch <= 0)
         return HVMS_ERR_INVALID_ARG;
-    return train_layout(batch).total;
+    return partial_bytes(batch);
 }
 
 int hvms_cdf_train(float *d_params, float *d_m, float *d_v, const int32_t *d_sorted, int64_t m,
@@ -453,13 +439,11 @@ int hvms_cdf_train(float *d_params, float *d_m, float *d_v, const int32_t *d_sor
 {
     if (!d_params || !d_m || !d_v || !d_sorted || m <= 0 || batch <= 0 || steps < 0)
         return HVMS_ERR_INVALID_ARG;
-    const TrainWs w = train_layout(batch);
-    int st = check(d_ws, ws_bytes, w.total);
+    int st = check(d_ws, ws_bytes, partial_bytes(batch));
     if (st)
         return st;
     hipStream_t s = (hipStream_t)stream;
-    char *ws = (char *)d_ws;
-    float *partial = (float *)(ws + w.bwd + bwd_layout(batch).partial);
+    float *partial = (float *)d_ws;
     const int rows = grad_rows(batch);
     hipLaunchKernelGGL(cdf_zero_kernel, dim3((NP + 255) / 256), dim3(256), 0, s, d_m, d_v);
     st = status(hipGetLastError());
