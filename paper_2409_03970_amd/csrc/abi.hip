@@ -274,18 +274,22 @@ int run_sort(bool pairs, const int32_t *kin, const int32_t *vin, int32_t *kout, 
 
 // A sort by the route its options, size and workspace allow: a workspace too
 // small for the digit passes (one sized for the merge passes by an explicit
-// option set) takes the merge passes.
+// option set) takes the merge passes; the fixed scratch of the allocation-free
+// sort takes digit passes over larger tiles first.
 int sort_any(int kind, const void *kin, const int32_t *vin, void *kout, int32_t *vout, int64_t n,
              void *ws, size_t ws_bytes, hipStream_t s, const Cfg &c, const hvms_options *opt,
-             KeyMap km = {})
+             KeyMap km = {}, bool fixed_scratch = false)
 {
-    if (radix_route(kind, n, opt) && (int64_t)ws_bytes >= radix_layout(kind, n).total) {
+    const bool route = radix_route(kind, n, opt);
+    const bool small_counts =
+        route && fixed_scratch && (int64_t)ws_bytes < radix_layout(kind, n).total;
+    if (route && (int64_t)ws_bytes >= radix_layout(kind, n, small_counts).total) {
         RadixIO io{};
         io.kin = kin;
         io.vin = vin;
         io.kout = kout;
         io.vout = vout;
-        return hip_status(launch_radix(kind, io, n, ws, km, s));
+        return hip_status(launch_radix(kind, io, n, ws, km, s, small_counts));
     }
     return run_sort(kind != RADIX_KEYS, (const int32_t *)kin, vin, (int32_t *)kout, vout, n, ws,
                     s, c, km);
@@ -402,7 +406,7 @@ int hvms_sort_i32_noalloc(const int32_t *d_in, int32_t *d_out, int64_t n, void *
             return st;
     }
     return sort_any(RADIX_KEYS, d_in, nullptr, d_out, nullptr, n, ws,
-                    HVMS_SORT_NOALLOC_SCRATCH_BYTES, (hipStream_t)stream, c, opt);
+                    HVMS_SORT_NOALLOC_SCRATCH_BYTES, (hipStream_t)stream, c, opt, KeyMap{}, true);
 }
 
 int hvms_sort_pairs_i32(const int32_t *d_keys_in, const int32_t *d_vals_in, int32_t *d_keys_out,

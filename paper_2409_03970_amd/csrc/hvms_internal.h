@@ -88,9 +88,10 @@ struct RadixLayout {
     int64_t a_k, a_v, b_k, b_v, a_p, ctl, totals, info, counts, rows, sample_pairs,
         groups, total;
 };
-RadixLayout radix_layout(int kind, int64_t n);
+// small_counts: large tiles at every size, whose counts take less room
+RadixLayout radix_layout(int kind, int64_t n, bool small_counts = false);
 hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap km,
-                        hipStream_t s);
+                        hipStream_t s, bool small_counts = false);
 
 // merge.hip
 bool merge_tile_supported(int tm, bool pairs);

@@ -1369,23 +1369,26 @@ constexpr Shape SHAPES[] = {{256, 8}, {512, 16}, {512, 32}, {1024, 16}, {512, 8}
 // threads from 5 * 2^23 on (4e7 doubles 1.35 ms with either tile, 5e7 1.70 ->
 // 1.65, 5e7 pairs with random values 1.92 -> 1.80), keys with payloads from 2^25
 // (0.96 -> 0.88 ms; 3e7 zipf keys 0.557 against 0.583, 2^26 keys 2.14 -> 1.87).
-int shape_of(int kind, int64_t n)
+// small_counts: 8,192-key tiles below 2^22 keys too, for a scratch that does not
+// hold the counts of four times as many tiles (3,850,241 to 4,194,303 keys 94-105
+// us, 92-94 with 2,048-key tiles, 215 by merge passes).
+int shape_of(int kind, int64_t n, bool small_counts)
 {
-    if (n < ((int64_t)1 << 22))
+    if (n < ((int64_t)1 << 22) && !small_counts)
         return n > ((int64_t)1 << 16) && n <= ((int64_t)1 << 17) ? 4 : 0;
     if (kind == RADIX_KEYS)
         return n >= ((int64_t)1 << 27) ? 2 : 1;
     return n >= (int64_t)(kind == RADIX_BY_KEY ? 4 : 5) << 23 ? 3 : 1;
 }
-int tile_of(int kind, int64_t n)
+int tile_of(int kind, int64_t n, bool small_counts)
 {
-    const Shape s = SHAPES[shape_of(kind, n)];
+    const Shape s = SHAPES[shape_of(kind, n, small_counts)];
     return s.nt * s.k;
 }
 
 // log2 of the tiles per chunk: at most MAX_CHUNKS chunks, half as many where
 // there are few tiles (whose counts then fit the fixed scratch of the
-// allocation-free sort beside 2^22 keys).
+// allocation-free sort beside 2^22 keys, see small_counts).
 int chunk_log2(int64_t tiles)
 {
     const int64_t most = tiles > 2 * MAX_CHUNKS ? MAX_CHUNKS : MAX_CHUNKS / 2;
@@ -1404,7 +1407,7 @@ static int sample_runs(int64_t n)
     return (int)(r < SAMPLE_RUNS_MAX ? r : SAMPLE_RUNS_MAX);
 }
 
-RadixLayout radix_layout(int kind, int64_t n)
+RadixLayout radix_layout(int kind, int64_t n, bool small_counts)
 {
     RadixLayout w{};
     int64_t off = 0;
@@ -1424,7 +1427,8 @@ RadixLayout radix_layout(int kind, int64_t n)
         w.a_p = off;
         off += align256(n * 8);
     }
-    const int64_t tiles = (n + tile_of(kind, n) - 1) / tile_of(kind, n);
+    const int tile = tile_of(kind, n, small_counts);
+    const int64_t tiles = (n + tile - 1) / tile;
     const int l = chunk_log2(tiles);
     const int64_t chunks = (tiles + ((int64_t)1 << l) - 1) >> l;
     w.ctl = off;
@@ -1519,9 +1523,9 @@ static hipError_t run_radix(RadixArgs a, bool inplace, hipStream_t s)
 }
 
 hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap km,
-                        hipStream_t s)
+                        hipStream_t s, bool small_counts)
 {
-    const RadixLayout w = radix_layout(kind, n);
+    const RadixLayout w = radix_layout(kind, n, small_counts);
     char *base = (char *)ws;
     RadixArgs a{};
     a.n = n;
@@ -1551,7 +1555,7 @@ hipError_t launch_radix(int kind, const RadixIO &io, int64_t n, void *ws, KeyMap
     a.map.x = (uint32_t)km.um ^ 0x80000000u;
     a.fl = (uint32_t)km.fl;
     const bool inplace = io.kin == io.kout || (io.vin && io.vin == io.vout);
-    const int shape = shape_of(kind, n);
+    const int shape = shape_of(kind, n, small_counts);
     switch (kind) {
     case RADIX_KEYS:
         return shape == 0   ? run_radix<RADIX_KEYS, 0, 6, 6>(a, inplace, s)
