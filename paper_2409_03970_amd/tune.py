@@ -59,7 +59,8 @@ def _entries(path):
     known = _parsed           # one tuple, replaced whole: safe with several threads
     if known[:2] != (path, ident):
         keys = ((k.rsplit(":", 1), v) for k, v in load_cache(path).items() if k.count(":") == 3)
-        known = _parsed = (path, ident, tuple((k[0], int(k[1]), v) for k, v in keys))
+        known = _parsed = (path, ident, tuple((k[0], int(k[1]), v) for k, v in keys
+                                              if k[1].isdecimal()))
     return known[2]
 
 
