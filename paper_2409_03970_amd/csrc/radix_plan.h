@@ -96,13 +96,14 @@ __host__ __device__ inline void scatter_modes(uint32_t *mode, uint32_t need, int
 
 // The low digits the first round leaves out, out of those in `need`: the most
 // without which the sample leaves an element alike with at most `most` other
-// ones on average, half a one up to 2^26 elements, one from 2^27 on.  m elements
-// in groups of g are m g / n of that, so one group of more than GROUP_MAX
-// elements is over the line up to 2^28, and groups that fill the list (longer
-// than half a window) are GROUPS_MAX * 33^2 / n of it or more.  Pairs of mixture
-// keys and random values, whose one key in 55 is the largest: 2^27 5.65 ms with
-// all eight passes, 5.15 with six and about 9,000 listed groups (merge sort
-// 5.42), 10^8 4.24 and 3.67; at 2^28, 65,536 groups, 11.9 and 12.4.
+// ones on average, half a one up to 2^26 elements, one at 2^27, two from 2^28 on
+// (less often another pass, a longer finish).  m elements in groups of g are
+// m g / n of that, so one group of more than GROUP_MAX elements is over the line
+// up to 1.9e8, and groups that fill the list (longer than half a window) are
+// GROUPS_MAX * 33^2 / n of it or more.  Pairs of mixture keys and random values,
+// whose one key in 55 is the largest, with all eight passes and with six (about
+// 9,000 listed groups at 2^27, 65,000 at 2^28): 10^8 4.20 and 3.67 ms, 2^27 5.62
+// and 4.97, 2.4e8 10.6 and 9.3, 2^28 11.8 and 10.4.
 //
 // The highest digit of `need` stays: where nearly all elements are equal, no
 // sampled neighbours differ in it, but a round without a step would never
@@ -117,7 +118,7 @@ __host__ __device__ inline uint32_t digits_to_drop(const Found &f, uint32_t need
 {
     const double pairs = 0.5 * f.runs * SAMPLE_LEN * SAMPLE_LEN;
     const double part = (double)f.n / 134217728.0;
-    const double most = part <= 0.5 ? 0.5 : part <= 1.0 ? part : 1.0;
+    const double most = part <= 0.5 ? 0.5 : part <= 2.0 ? part : 2.0;
     uint32_t limit = 7;
     if ((double)f.same[7] * 2048.0 >= (double)f.runs * SAMPLE_LEN)
         limit = f.near0 != ~0u   ? (31 - __builtin_clz(f.near0 + 1)) >> 3

@@ -150,7 +150,7 @@ def test_heavy_value_and_its_like(plan, kind, digit):
 
 
 @pytest.mark.parametrize("n,most", ((1 << 24, 0.5), (1 << 26, 0.5), (3 << 25, 0.75), (1 << 27, 1.0),
-                                    (1 << 28, 1.0)))
+                                    (3 << 26, 1.5), (1 << 28, 2.0), (1 << 30, 2.0)))
 def test_how_much_may_be_left_alike(plan, n, most):
     x = _words(255, np.random.default_rng(3))
     line = int(most * RUNS * 8192**2 / 2 / n)             # sampled neighbours alike
