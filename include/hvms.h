@@ -141,7 +141,8 @@ int hvms_last_hip_error(void);
  * passes: keys alone and sorts by key past 2^15 keys, pairs and 64-bit keys
  * from 2^22.  The result is the same bit for bit.  Any option set
  * (a tile shape, a co-rank mode, stats, events, ...) keeps the merge sort, and
- * so does a workspace that only holds what the merge sort needs.
+ * so does a workspace that only holds what the merge sort needs.  What the
+ * calls below say of merges, block stage and index arrays is the merge sort.
  */
 
 /* Bytes of workspace hvms_sort_i32 / hvms_sort_pairs_i32 need for n keys
@@ -248,7 +249,9 @@ int hvms_sort_pairs_f32(const float *d_keys_in, const int32_t *d_vals_in,
  *                   per key plus co-ranks once n exceeds one block tile),
  *                   256-byte aligned.
  * Tuning values are those of hvms_sort_pairs_i32 (merge_variant 4 is not
- * available).  n == 0 is a no-op.
+ * available).  n == 0 is a no-op.  Digit passes (from 2^22 keys with no option
+ * set) read the packed array in their first pass and write it in their last,
+ * and need as many bytes per key.
  */
 int64_t hvms_sort64_workspace_bytes(int64_t n, const hvms_options *opt);
 int hvms_sort_i64(const int64_t *d_in, int64_t *d_out, int64_t n, void *d_ws,
@@ -263,7 +266,9 @@ int hvms_sort_f64(const double *d_in, double *d_out, int64_t n, void *d_ws,
  * on (key, input index) pairs) carrying one 64-bit value each
  * (any 8-byte type: int64, uint64, double, a pointer).  d_keys_out is the
  * ascending arrangement of d_keys_in; d_vals_out[i] is the payload that
- * came with d_keys_out[i]; keys that are equal keep their input order.  The
+ * came with d_keys_out[i]; keys that are equal keep their input order.  Past
+ * 2^15 keys with no option set, digit passes move key and payload together
+ * (d_vals_out also holds what the passes in between write).  Otherwise the
  * keys are sorted together with their input indices by the key-value sort
  * (indices made in the block stage, never read from memory), then one pass
  * moves the payloads: d_vals_out[i] = d_vals_in[index[i]].
@@ -273,7 +278,8 @@ int hvms_sort_f64(const double *d_in, double *d_out, int64_t n, void *d_ws,
  *   n               0 <= n <= 2^31 - 1 (indices are int32).
  *   d_ws/ws_bytes   workspace, >= hvms_sort_by_key_workspace_bytes(n, opt)
  *                   (4 bytes per key for the indices plus the key-value
- *                   sort's workspace), 256-byte aligned.
+ *                   sort's workspace, which is what the digit passes' keys,
+ *                   payloads and counts need too), 256-byte aligned.
  * Tuning values are those of hvms_sort_pairs_i32.  n == 0 is a no-op.
  */
 int64_t hvms_sort_by_key_workspace_bytes(int64_t n, const hvms_options *opt);
@@ -423,7 +429,8 @@ int hvms_cdf_sample_i32(const int32_t *d_keys, int64_t n, int64_t m, uint64_t se
  * target of the i-th key is i/m.  Runs `steps` Adam steps (lr, betas 0.9 /
  * 0.999, eps 1e-8) on minibatches of `batch` sample positions drawn with
  * SplitMix64 from `seed`.  d_params holds the initial parameters on entry and
- * the trained ones on exit; d_m, d_v are zeroed by the call.
+ * the trained ones on exit; d_m, d_v are zeroed by the call.  Workspace: the
+ * partial sums of at most 256 workgroups, 1.2 MB, whatever the batch.
  */
 int64_t hvms_cdf_train_workspace_bytes(int64_t batch);
 int hvms_cdf_train(float *d_params, float *d_m, float *d_v, const int32_t *d_sorted,

@@ -26,8 +26,9 @@
 // The scatter takes 0.61 ms (0.58 in the first pass, see `spread`) for
 // 2.15 GB: with its ranks left out and its writes made linear it would take
 // 0.39, with the writes alone linear 0.52, so both the partial cache lines at
-// the ends of the runs and the 55 VALU operations per key (32 of them the
-// ballots) show.  Run ends are why the tile is as large as two workgroups
+// the ends of the runs (8 % more bytes written than the keys have) and the 60
+// VALU operations per key (32 of them the ballots; 28 in the first pass; 0.41 ms
+// at the rate of all SIMDs) show.  Run ends are why the tile is as large as two workgroups
 // per CU allow (16,384 keys, runs of 64: 0.665 against 0.79 ms at 8,192),
 // and why the tiles are dealt so that an XCD's workgroups walk one contiguous
 // range together: the line that two tiles' runs share is completed in that
@@ -680,9 +681,10 @@ template <int KIND> __global__ __launch_bounds__(SAMPLE_LEN / 8) void radix_samp
 // group is read through and, if it is out of order, put on a list for
 // radix_groups; past GROUP_MAX elements, or past the end of the list, the
 // sort goes to the second round.  What others look at while an element moves,
-// the common digits of its group, does not change.  Bound by one read of the
-// elements (2^28 uniform pairs, 12 % of them alike: 2.5 ms when the first
-// lane of each group read it through in memory, now 1.0).
+// the common digits of its group, does not change.  Bound by its instructions
+// (5e7 doubles 0.22 ms: 122 VALU and 20 LDS operations an element, for a read of
+// 0.09 ms; 2^28 uniform pairs, 12 % of them alike: 2.5 ms when the first lane of
+// each group read it through in memory, now 1.0).
 constexpr int GROUP_MAX = 16384;    // elements of a listed group: the LDS of one workgroup
 constexpr int GROUPS_MAX = 131072;  // listed groups
 
@@ -1384,8 +1386,8 @@ constexpr Shape SHAPES[] = {{256, 8}, {512, 16}, {512, 32}, {1024, 16}, {512, 8}
 // there are at most FEW_TILES (32) of them, whose sums cost a workgroup less
 // than the scan launch (2^16 keys 51 -> 42 us, 100,003 keys 53 -> 43; 64 tiles
 // of 2,048 keys 52 -> 50, 128 52 -> 64); keys alone large ones once
-// the runs go to HBM (2^26 keys 0.78 against 0.80 ms, 2^28 keys 3.78 against
-// 3.40).  Two words a key at K = 32 would spill; they take 16,384 with 1024
+// the runs go to HBM (2^25 keys 0.40 against 0.43 ms, 2^26 0.77 with either tile,
+// 2^27 1.74 -> 1.51, 2^28 3.72 -> 3.10).  Two words a key at K = 32 would spill; they take 16,384 with 1024
 // threads from 5 * 2^23 on (4e7 doubles 1.35 ms with either tile, 5e7 1.70 ->
 // 1.65, 5e7 pairs with random values 1.92 -> 1.80), keys with payloads from 2^25
 // (0.96 -> 0.88 ms; 3e7 zipf keys 0.557 against 0.583, 2^26 keys 2.14 -> 1.87).
